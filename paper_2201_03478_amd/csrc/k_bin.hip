@@ -49,12 +49,20 @@ __device__ __forceinline__ void anchor_of(const double *ptg, int64_t s, const Bi
 // per key instead of per sample): rank = global base + local rank.  Keys that find
 // no free slot within the probe limit take a global rank directly.  Ranges of
 // different workgroups, and direct ranks, are disjoint by construction.
+// SPT samples per thread: long passes take spans of 16384 samples (about 8 scan
+// circles), so a scan's keys are counted mostly in LDS; with spans of 4096 or 1024 the
+// global atomics of retraced cells cost more than the idle CUs (lmax 512, 1e7 scan
+// samples, whole interpolation: 1.03 ms against 1.21 and 1.52 ms).  Passes below 2^19
+// samples take 4096 and below 2^17 1024: their few workgroups are what bounds them (2e5
+// scan samples at lmax 128: 74 against 81 us).  Samples that are spread evenly overflow
+// the table: the short probe limit sends them to the global counter early (1e5 uniform
+// pointings: this kernel 193 us in spans of 16384 with 64 probes, 8 us now).
 constexpr int KEYS_NT = 1024;        // threads per workgroup
-constexpr int KEYS_SPT = 16;         // samples per thread (a span of 16384 samples)
-constexpr int KEYS_HT = 4096;        // hash slots
-constexpr int KEYS_PROBE = 64;       // linear-probe limit
+constexpr int KEYS_HT = 8192;        // hash slots
+constexpr int KEYS_PROBE = 8;       // linear-probe limit
 constexpr int KEYS_EMPTY = -1;
 
+template <int KEYS_SPT>
 __global__ void __launch_bounds__(KEYS_NT) k_bin_keys(const double *__restrict__ ptg, int64_t n, BinGeom g,
                                                       int *__restrict__ key, int *__restrict__ rank,
                                                       int *__restrict__ count) {
@@ -86,7 +94,7 @@ __global__ void __launch_bounds__(KEYS_NT) k_bin_keys(const double *__restrict__
         slot[i] = -1;
         lr[i] = 0;
         if (k >= 0) {
-            int h = (int)(((unsigned)k * 2654435761u) >> 20) & (KEYS_HT - 1);
+            int h = (int)(((unsigned)k * 2654435761u) >> 19) & (KEYS_HT - 1);
             for (int q = 0; q < KEYS_PROBE; ++q) {
                 int cur = hkey[h];
                 if (cur == KEYS_EMPTY) cur = atomicCAS(&hkey[h], KEYS_EMPTY, k);
@@ -310,16 +318,19 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     const int64_t nkeys = (int64_t)g.nkr * g.nkc;
     const int bs = 256;
     const unsigned gs = (unsigned)((n + bs - 1) / bs);
+    const int chunk = p->bin_chunk;
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
-    const unsigned gk = (unsigned)((n + KEYS_NT * KEYS_SPT - 1) / (KEYS_NT * KEYS_SPT));
-    hipLaunchKernelGGL(k_bin_keys, dim3(gk), dim3(KEYS_NT), 0, p->stream, ptg, n, g, w.key, w.rank, w.count);
+    const int spt = n >= (1 << 19) ? 16 : n >= (1 << 17) ? 4 : 1;
+    const unsigned gk = (unsigned)((n + KEYS_NT * spt - 1) / (KEYS_NT * spt));
+    auto keys = spt == 16 ? k_bin_keys<16> : spt == 4 ? k_bin_keys<4> : k_bin_keys<1>;
+    hipLaunchKernelGGL(keys, dim3(gk), dim3(KEYS_NT), 0, p->stream, ptg, n, g, w.key, w.rank, w.count);
     const int nblk = (int)((nkeys + SCAN_BLOCK - 1) / SCAN_BLOCK);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, p->bin_chunk);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, chunk);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_NT), 0, p->stream, w.sums, nblk, w.totals);
     hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, w.offs,
-                       p->bin_chunk);
+                       chunk);
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
     hipLaunchKernelGGL(k_bin_items, dim3((unsigned)((nkeys + bs - 1) / bs)), dim3(bs), 0, p->stream, w.count,
-                       w.offs, nkeys, w.items, p->bin_chunk);
+                       w.offs, nkeys, w.items, chunk);
     return hipGetLastError();
 }
