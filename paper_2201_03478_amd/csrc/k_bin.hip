@@ -15,6 +15,8 @@
 //
 // Integer index arithmetic is exact; the fractional offsets u - floor(u) are
 // kept in FP64 (the FP32 gather rounds them when it forms its weights).
+#include <algorithm>
+
 #include "sc_common.h"
 
 namespace {
@@ -318,7 +320,8 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     const int64_t nkeys = (int64_t)g.nkr * g.nkc;
     const int bs = 256;
     const unsigned gs = (unsigned)((n + bs - 1) / bs);
-    const int chunk = p->bin_chunk;
+    int chunk = p->bin_chunk;
+    if (p->prec == SC_FP64) chunk = std::min(chunk, BIN_CHUNK_64);
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
     const int spt = n >= (1 << 19) ? 16 : n >= (1 << 17) ? 4 : 1;
     const unsigned gk = (unsigned)((n + KEYS_NT * spt - 1) / (KEYS_NT * spt));

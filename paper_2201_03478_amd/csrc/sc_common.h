@@ -38,6 +38,8 @@ struct FftPlan {
 // Default samples per work item of the binned gather, and samples per binning pass
 // (a pass of 2^27 samples holds about 7.5 GB of binning workspace, 56 bytes per sample).
 #define BIN_CHUNK 256
+// ... of the FP64 gather, whose wave takes one item: up to four 16-sample tiles.
+#define BIN_CHUNK_64 64
 #define BIN_PASS_MAX (1 << 27)
 
 // Anchor grid of the binned gather: key = row0 * nkc + col0.
