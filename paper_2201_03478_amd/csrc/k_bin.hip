@@ -313,7 +313,7 @@ hipError_t sc_launch_count_nonfinite(const void *x, int64_t n, int f32, int *cou
     return hipGetLastError();
 }
 
-hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y) {
+hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y, bool scatter64) {
     BinWork &w = p->bw;
     w.last_n = n;
     const BinGeom g = sc_bin_geom(p);
@@ -321,7 +321,7 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     const int bs = 256;
     const unsigned gs = (unsigned)((n + bs - 1) / bs);
     int chunk = p->bin_chunk;
-    if (p->prec == SC_FP64) chunk = std::min(chunk, BIN_CHUNK_64);
+    if (p->prec == SC_FP64) chunk = std::min(chunk, scatter64 ? BIN_CHUNK_SC64 : BIN_CHUNK_64);
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
     const int spt = n >= (1 << 19) ? 16 : n >= (1 << 17) ? 4 : 1;
     const unsigned gk = (unsigned)((n + KEYS_NT * spt - 1) / (KEYS_NT * spt));

@@ -16,8 +16,9 @@
 //    weight w_s(t) = w_theta(t / 8) w_phi(t % 8) is formed from the 1-d weights
 //    in LDS as the matrix operand is read.  The atomics are not what limits it:
 //    without them the kernel takes within 2% of the time.
-//  * k_scatter_direct (any W, FP32 or FP64): one wave per sample, lanes over
-//    components, one atomic per (tap, component, sample).
+//  * k_scatter_mfma64 (FP64 maps): the same product in FP64 for every even W.
+//  * k_scatter_direct (FP32 maps with W != 8, and the forced per-sample path): one wave
+//    per sample, lanes over components, one atomic per (tap, component, sample).
 #include "sc_common.h"
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -401,6 +402,164 @@ k_scatter_split(const int4 *__restrict__ items, int *__restrict__ totals, const 
     }
 }
 
+// FP64 plans: the patch gradients as v_mfma_f64_16x16x4_f64 products (FP64 products and
+// accumulation).  PG[t][c] = sum_s w_s(t) V[s][c] with a tile of 16 taps (16 columns of
+// one row of the stencil, two rows at W <= 8, four at W = 4) x 16 components; operand
+// layout A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k, D[i][j] in lane
+// j + 16 (i % 4), element i / 4.  A workgroup takes items of at most S64 samples: their
+// 1-d weights stay in LDS for every sweep over two component tiles, V is formed 64
+// samples at a time, and wave w owns tap tiles w, w + 4, ...  One FP64 atomic per
+// (tap, component, item): the sample-by-sample form (k_scatter_direct) issues one per
+// (tap, component, sample) and is bound by them.  lmax 128, kmax 8, W = 14, 2e5 scan
+// samples: 6.23 ms sample by sample (7.1e8 atomics), 0.13 ms here.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int S64 = BIN_CHUNK_SC64;  // samples per item
+constexpr int S64R = S64 + 4; // row stride of the weights: eight tap rows x four samples in distinct banks
+
+template <int W>
+struct Sc64 {
+    static constexpr int RPT = W <= 4 ? 4 : W <= 8 ? 2 : 1;  // stencil rows per tap tile
+    static constexpr int NT = (W + RPT - 1) / RPT;           // tap tiles
+    static constexpr int TW = (NT + 3) / 4;                  // per wave
+    static constexpr int NVS = 48;                           // row stride of V (two tiles + padding)
+    static constexpr size_t lds() {
+        return sizeof(double) * (2 * W * S64R + 64 * NVS + S64) + sizeof(double2) * S64;
+    }
+};
+
+template <int W, int N>
+__device__ __forceinline__ void scatter64_sweep(const double *Wt, double *V, const double2 *E1, const double *Ys, int ns,
+                                                int cbase, double *__restrict__ gm, int cols, int ncp, int ncomp) {
+    using C = Sc64<W>;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int r = lane & 15, grp = lane >> 4;
+    const int tr = r / W, tc = r - tr * W;  // tap r of a tile: row tr, column tc
+    const bool on = tr < C::RPT && r < C::RPT * W;
+    const double *wph = Wt + (W + (on ? tc : 0)) * S64R + grp;
+    const double *wth[C::TW];
+#pragma unroll
+    for (int q = 0; q < C::TW; ++q) {
+        const int row = (wv + 4 * q) * C::RPT + (on ? tr : 0);
+        wth[q] = Wt + (row < W ? row : W - 1) * S64R + grp;  // past the stencil: left out below
+    }
+    doublex4 acc[C::TW][N];
+#pragma unroll
+    for (int q = 0; q < C::TW; ++q)
+#pragma unroll
+        for (int c = 0; c < N; ++c) acc[q][c] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int s0 = 0; s0 < ns; s0 += 64) {
+        __syncthreads();  // V's readers (and, first, the weights' writers) are done
+        {
+            // V[s][c] = y_s basis_c(psi_s): 4 lanes per sample, 2 N orders each; zero past ns
+            const int sl = tid >> 2, k0 = (cbase >> 1) + 2 * N * (tid & 3);
+            const bool in = s0 + sl < ns;
+            const double2 e1 = in ? E1[s0 + sl] : make_double2(0.0, 0.0);
+            const double yy = in ? Ys[s0 + sl] : 0.0;
+            double2 z = cpow_int(e1, k0);
+            double *v = V + sl * C::NVS + 4 * N * (tid & 3);
+#pragma unroll
+            for (int j = 0; j < 2 * N; ++j) {
+                v[2 * j] = yy * z.x;
+                v[2 * j + 1] = yy * z.y;
+                z = cmul(z, e1);
+            }
+            if (!in)
+#pragma unroll
+                for (int j = 0; j < 4 * N; ++j) v[j] = 0.0;
+        }
+        __syncthreads();
+        const int nk = (ns - s0 < 64 ? ns - s0 + 3 : 64) >> 2;
+        const double *vb = V + grp * C::NVS + r;
+#pragma unroll 2
+        for (int ks = 0; ks < nk; ++ks) {
+            double b[N];
+#pragma unroll
+            for (int c = 0; c < N; ++c) b[c] = vb[4 * ks * C::NVS + 16 * c];
+            const double wf = wph[s0 + 4 * ks];
+#pragma unroll
+            for (int q = 0; q < C::TW; ++q) {
+                const double a = wth[q][s0 + 4 * ks] * wf;
+#pragma unroll
+                for (int c = 0; c < N; ++c) acc[q][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c], acc[q][c], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < C::TW; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int t = 4 * v + grp;  // tap of the tile
+            const int row = (wv + 4 * q) * C::RPT + t / W, col = t - (t / W) * W;
+            if (t >= C::RPT * W || row >= W) continue;
+            double *base = gm + ((size_t)row * cols + col) * ncp;
+#pragma unroll
+            for (int c = 0; c < N; ++c) {
+                const int cc = cbase + 16 * c + r;
+                if (cc < ncomp && cc != 1) atomic_add(base + cc, acc[q][c][v]);  // basis_1 = sin 0 = 0
+            }
+        }
+}
+
+template <int W>
+__global__ void __launch_bounds__(256)
+k_scatter_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals, const BinRec *__restrict__ rec,
+                 const double *__restrict__ y, double *__restrict__ gmaps, int cols, int ncp, int ncomp, int nkc,
+                 double beta) {
+    using C = Sc64<W>;
+    extern __shared__ __attribute__((aligned(16))) double smem_d[];
+    double2 *E1 = (double2 *)smem_d;         // [S64] e^{i psi}
+    double *Ys = (double *)(E1 + S64);       // [S64]
+    double *Wt = Ys + S64;                   // [2 W][S64R]: theta weights, then phi weights
+    double *V = Wt + 2 * W * S64R;           // [64][NVS]
+    const int tid = threadIdx.x;
+    const int nitems = totals[1];
+    const int nct = (ncomp + 15) >> 4;
+    for (int it = xcd_remap(blockIdx.x, gridDim.x); it < nitems; it += gridDim.x) {
+        const int4 item = items[it];
+        const int row0 = item.x / nkc, col0 = item.x - (item.x / nkc) * nkc;
+        double *gm = gmaps + ((size_t)row0 * cols + col0) * ncp;
+        for (int ch = 0; ch < item.z; ch += S64) {
+            const int ns = item.z - ch < S64 ? item.z - ch : S64;
+            const BinRec *rc = rec + item.y + ch;
+            if (tid < ns) {
+                double sn, cs;
+                sincos(rc[tid].psi, &sn, &cs);
+                E1[tid] = make_double2(cs, sn);
+                Ys[tid] = y[rc[tid].idx];
+            }
+            const int nsp = (ns + 3) & ~3;  // whole steps of four samples
+            for (int e = tid; e < 2 * W * S64; e += 256) {
+                const int node = e / S64, sl = e - node * S64;
+                if (sl < nsp) {
+                    double w = 0.0;
+                    if (sl < ns) {
+                        const bool th = node < W;
+                        const double f = th ? rc[sl].fu : rc[sl].fv;
+                        w = es_w<double>((f + (double)(W / 2 - 1 - (th ? node : node - W))) / (double)(W / 2), beta);
+                    }
+                    Wt[node * S64R + sl] = w;
+                }
+            }
+            int ct = 0;
+            for (; ct + 2 <= nct; ct += 2) scatter64_sweep<W, 2>(Wt, V, E1, Ys, ns, 16 * ct, gm, cols, ncp, ncomp);
+            if (ct < nct) scatter64_sweep<W, 1>(Wt, V, E1, Ys, ns, 16 * ct, gm, cols, ncp, ncomp);
+            __syncthreads();  // weights and phases are rewritten by the next samples
+        }
+    }
+}
+
+template <int W>
+hipError_t launch_scatter_mfma64(sc_plan *p, const double *y, double *gmaps) {
+    const size_t lds = Sc64<W>::lds();
+    auto kern = k_scatter_mfma64<W>;
+    hipError_t e = sc_set_lds_attr((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    const int grid = sc_persistent_grid((const void *)kern, 256, lds, p->gather_wgs_per_cu);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, p->stream, p->bw.items, p->bw.totals, p->bw.sorted.rec, y, gmaps,
+                       p->cols, p->ncp, p->ncomp, sc_bin_geom(p).nkc, p->beta);
+    return hipGetLastError();
+}
+
 // Deterministic mode, sample order.  The binning ranks the samples of an anchor in
 // the order its atomics happen to run, so the same samples can land in different
 // 64-sample chunks from run to run.  In this mode every anchor is one work item and
@@ -596,6 +755,23 @@ hipError_t sc_launch_scatter_reduce(sc_plan *p, void *gmaps) {
     if (ct <= 9) return launch_reduce<9>(p, gmaps);
     if (ct <= 13) return launch_reduce<13>(p, gmaps);
     return launch_reduce<16>(p, gmaps);
+}
+
+// FP64 plans: the binned scatter of one pass (after sc_launch_binning in adjoint form without y).
+bool sc_scatter64_supported(const sc_plan *p) {
+    return p->prec == SC_FP64 && p->W >= 4 && p->W <= 16 && (p->W & 1) == 0 && p->ncomp <= 256 && !p->gather_direct;
+}
+hipError_t sc_launch_scatter64(sc_plan *p, const double *y, double *gmaps) {
+    switch (p->W) {
+        case 4: return launch_scatter_mfma64<4>(p, y, gmaps);
+        case 6: return launch_scatter_mfma64<6>(p, y, gmaps);
+        case 8: return launch_scatter_mfma64<8>(p, y, gmaps);
+        case 10: return launch_scatter_mfma64<10>(p, y, gmaps);
+        case 12: return launch_scatter_mfma64<12>(p, y, gmaps);
+        case 14: return launch_scatter_mfma64<14>(p, y, gmaps);
+        case 16: return launch_scatter_mfma64<16>(p, y, gmaps);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // Scatter of one pass (binned: binning with the pass's TOD gradient already done).

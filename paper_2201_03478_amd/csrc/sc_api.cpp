@@ -926,10 +926,29 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
                 off += cnt;
             }
         } else {
-            slot = timing_begin(p, SC_STAGE_SCATTER);
-            e = sc_launch_scatter(p, ptg, n, tod_grad, p->gmaps);
-            timing_end(p, slot);
-            if (e != hipSuccess) return hip_fail(e, "scatter launch");
+            // FP64: binned on the matrix cores; sample by sample if the binning workspace cannot
+            // be had (or the plan takes the per-sample path)
+            const int64_t pass = n < p->bin_pass_max ? n : p->bin_pass_max;
+            const bool binned = sc_scatter64_supported(p) && ensure_bin_work(p, pass) == SC_OK;
+            if (binned) {
+                for (int64_t off = 0; off < n; off += pass) {
+                    const int64_t cnt = n - off < pass ? n - off : pass;
+                    slot = timing_begin(p, SC_STAGE_BIN);
+                    e = sc_launch_binning(p, ptg + 3 * off, cnt, nullptr, true);
+                    timing_end(p, slot);
+                    if (e != hipSuccess) return hip_fail(e, "binning launch");
+                    slot = timing_begin(p, SC_STAGE_SCATTER);
+                    e = sc_launch_scatter64(p, (const double *)tod_grad + off, (double *)p->gmaps);
+                    timing_end(p, slot);
+                    if (e != hipSuccess) return hip_fail(e, "scatter launch");
+                }
+            } else {
+                g_msg[0] = 0;
+                slot = timing_begin(p, SC_STAGE_SCATTER);
+                e = sc_launch_scatter(p, ptg, n, tod_grad, p->gmaps);
+                timing_end(p, slot);
+                if (e != hipSuccess) return hip_fail(e, "scatter launch");
+            }
         }
     }
     slot = timing_begin(p, SC_STAGE_ADJ_FFT);

@@ -40,6 +40,8 @@ struct FftPlan {
 #define BIN_CHUNK 256
 // ... of the FP64 gather, whose wave takes one item: up to four 16-sample tiles.
 #define BIN_CHUNK_64 64
+// ... of the FP64 scatter, whose workgroup keeps one item's weights in LDS.
+#define BIN_CHUNK_SC64 128
 #define BIN_PASS_MAX (1 << 27)
 
 // Anchor grid of the binned gather: key = row0 * nkc + col0.
@@ -248,13 +250,16 @@ hipError_t sc_launch_scatter_reduce(sc_plan *p, void *gmaps);  // deterministic 
 hipError_t sc_launch_det_order(sc_plan *p, int nitems);         // deterministic mode, after the binning
 int sc_det_max_items();                                         // largest anchor it orders
 bool sc_scatter_binned_supported(const sc_plan *p);
+bool sc_scatter64_supported(const sc_plan *p);
+hipError_t sc_launch_scatter64(sc_plan *p, const double *y, double *gmaps);
 hipError_t sc_launch_zero(void *dst, size_t bytes, hipStream_t stream);
 // Adds to *count the number of NaN or infinite values among x[0 .. n) (double, or float with f32).
 hipError_t sc_launch_count_nonfinite(const void *x, int64_t n, int f32, int *count, hipStream_t stream);
 hipError_t sc_launch_gather(sc_plan *p, const double *ptg, int64_t n, void *tod);
 // Sort samples into anchor order (k_bin.hip).  With y (FP32 adjoint passes) the
 // records take the adjoint layout AdjRec instead of BinRec.
-hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y = nullptr);
+// scatter64: items of the FP64 scatter instead of the gather's.
+hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y = nullptr, bool scatter64 = false);
 hipError_t sc_launch_dipole(const double *blm, int lmax, int kmax, const double *ptg, int64_t n, const double *beta,
                             int64_t spp, double T0, double q, double *out, hipStream_t stream);
 hipError_t sc_launch_gather_binned(sc_plan *p, void *tod);
