@@ -11,7 +11,10 @@
 //   k_scan_*       exclusive scan of (samples, work items) per key
 //   k_bin_scatter  sample records in key order: fractional offsets and psi
 //                  (FP64) and the original index, 32 bytes each
-//   k_bin_items    work items (key, first sorted sample, count <= the plan's bin chunk)
+//   k_bin_items    work items (key, first sorted sample, count <= the plan's bin chunk);
+//                  for the split gather, anchors of at most BIN_SHORT samples are listed
+//                  apart, from the end of the item array down
+//   k_bin_small    all of it in one workgroup, for passes of at most BIN_SMALL samples
 //
 // Integer index arithmetic is exact; the fractional offsets u - floor(u) are
 // kept in FP64 (the FP32 gather rounds them when it forms its weights).
@@ -128,10 +131,10 @@ constexpr int SCAN_NT = 256;
 constexpr int SCAN_PER = 16;
 constexpr int SCAN_BLOCK = SCAN_NT * SCAN_PER;
 
-__device__ __forceinline__ int2 key_pair(const int *count, int64_t i, int64_t nkeys, int chunk) {
+__device__ __forceinline__ int2 key_pair(const int *count, int64_t i, int64_t nkeys, int chunk, int shortn) {
     if (i >= nkeys) return make_int2(0, 0);
     const int c = count[i];
-    return make_int2(c, (c + chunk - 1) / chunk);
+    return make_int2(c, c <= shortn ? 0 : (c + chunk - 1) / chunk);  // short anchors are listed apart
 }
 
 // block-wide exclusive scan of one int2 per thread; returns the block total
@@ -154,12 +157,12 @@ __device__ int2 block_scan(int2 v, int2 *sh, int &excl_x, int &excl_y) {
 }
 
 __global__ void __launch_bounds__(SCAN_NT) k_scan_reduce(const int *__restrict__ count, int64_t nkeys,
-                                                         int2 *__restrict__ sums, int chunk) {
+                                                         int2 *__restrict__ sums, int chunk, int shortn) {
     __shared__ int2 sh[SCAN_NT];
     const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + (int64_t)threadIdx.x * SCAN_PER;
     int2 acc = make_int2(0, 0);
     for (int q = 0; q < SCAN_PER; ++q) {
-        const int2 v = key_pair(count, base + q, nkeys, chunk);
+        const int2 v = key_pair(count, base + q, nkeys, chunk, shortn);
         acc.x += v.x;
         acc.y += v.y;
     }
@@ -185,18 +188,19 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan_sums(int2 *__restrict__ sums, 
         totals[0] = carry.x;  // samples
         totals[1] = carry.y;  // work items
         totals[2] = 0;        // work-queue cursor of the gather
+        totals[3] = 0;        // short items
     }
 }
 
 __global__ void __launch_bounds__(SCAN_NT) k_scan_apply(const int *__restrict__ count, int64_t nkeys,
                                                         const int2 *__restrict__ sums, int2 *__restrict__ offs,
-                                                        int chunk) {
+                                                        int chunk, int shortn) {
     __shared__ int2 sh[SCAN_NT];
     const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + (int64_t)threadIdx.x * SCAN_PER;
     int2 v[SCAN_PER];
     int2 acc = make_int2(0, 0);
     for (int q = 0; q < SCAN_PER; ++q) {
-        v[q] = key_pair(count, base + q, nkeys, chunk);
+        v[q] = key_pair(count, base + q, nkeys, chunk, shortn);
         acc.x += v[q].x;
         acc.y += v[q].y;
     }
@@ -211,6 +215,20 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan_apply(const int *__restrict__ 
     }
 }
 
+// The four 8-byte words of a sample's record: BinRec, or with y the adjoint layout.
+struct RecWords {
+    double w[4];
+};
+__device__ __forceinline__ double word2(int lo, int hi) {
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ RecWords make_rec(double fu, double fv, double psi, int s, const float *__restrict__ y) {
+    if (!y) return RecWords{{fu, fv, psi, word2(s, 0)}};
+    double sn, cs;
+    sincos(psi, &sn, &cs);
+    return RecWords{{word2(__float_as_int((float)fu), __float_as_int((float)fv)), cs, sn, word2(__float_as_int(y[s]), s)}};
+}
+
 // Sample records in anchor order.  Lane pairs write the two 16-byte halves of one
 // record in the same instruction (one 32-byte run per sample, not four partial
 // writes); the values come from the sample's own lane by shuffles.  (Blocks are
@@ -223,22 +241,13 @@ __global__ void k_bin_scatter(const double *__restrict__ ptg, int64_t n, BinGeom
     const int64_t s = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const bool valid = s < n;
     int pos = -1;
-    double fu = 0.0, fv = 0.0, psi = 0.0, yv = 0.0;
+    RecWords rw = {{0.0, 0.0, 0.0, 0.0}};
     if (valid) {
         int r0, c0;
+        double fu, fv, psi;
         anchor_of(ptg, s, g, r0, c0, fu, fv, psi);
         pos = offs[key[s]].x + rank[s];
-        if (y) {
-            // adjoint layout: (fu, fv as FP32; cos psi) and (sin psi; y, idx)
-            double sn, cs;
-            sincos(psi, &sn, &cs);
-            fu = __longlong_as_double((long long)(((unsigned long long)(unsigned)__float_as_int((float)fv) << 32) |
-                                                  (unsigned)__float_as_int((float)fu)));
-            fv = cs;
-            psi = sn;
-            yv = __longlong_as_double((long long)(((unsigned long long)(unsigned)(int)s << 32) |
-                                                  (unsigned)__float_as_int(y[s])));
-        }
+        rw = make_rec(fu, fv, psi, (int)s, y);
     }
     const int lane = threadIdx.x & 63;
     const int hi = lane & 1;
@@ -247,27 +256,136 @@ __global__ void k_bin_scatter(const double *__restrict__ ptg, int64_t n, BinGeom
     for (int half = 0; half < 2; ++half) {
         const int src = (lane >> 1) + 32 * half;  // the wave lane whose sample this lane writes
         const int p = __shfl(pos, src);
-        const double su = __shfl(fu, src), sv = __shfl(fv, src), sp = __shfl(psi, src), sy = __shfl(yv, src);
-        const int64_t sidx = s - lane + src;
+        const double w0 = __shfl(rw.w[0], src), w1 = __shfl(rw.w[1], src);
+        const double w2 = __shfl(rw.w[2], src), w3 = __shfl(rw.w[3], src);
         if (p >= 0) {
-            // low half (fu, fv); high half (psi, idx in the low word and pad 0); or the adjoint layout
-            const double2 v = hi ? make_double2(sp, y ? sy : __longlong_as_double((long long)(unsigned)sidx))
-                                 : make_double2(su, sv);
+            const double2 v = hi ? make_double2(w2, w3) : make_double2(w0, w1);
             rec2[2 * (size_t)p + hi] = v;
         }
     }
 }
 
 __global__ void k_bin_items(const int *__restrict__ count, const int2 *__restrict__ offs, int64_t nkeys,
-                            int4 *__restrict__ items, int chunk) {
+                            int4 *__restrict__ items, int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nkeys) return;
-    const int c = count[k];
-    if (c == 0) return;
+    const int c = k < nkeys ? count[k] : 0;
+    if (shortn > 0) {
+        // one reservation per wave, so neighbouring anchors stay neighbours in the list
+        const bool is = c > 0 && c <= shortn;
+        const unsigned long long mask = __ballot(is);
+        const int lane = threadIdx.x & 63;
+        int base = 0;
+        if (mask && lane == 0) base = atomicAdd(&totals[3], __popcll(mask));
+        base = __shfl(base, 0);
+        if (is) {
+            const int i = base + __popcll(mask & ((1ull << lane) - 1));
+            items[cap - 1 - i] = make_int4((int)k, offs[k].x, c, 0);
+        }
+    }
+    if (c <= shortn) return;
     const int2 o = offs[k];
     for (int q = 0; q * chunk < c; ++q) {
         const int cnt = c - q * chunk < chunk ? c - q * chunk : chunk;
         items[o.y + q] = make_int4((int)k, o.x + q * chunk, cnt, 0);
+    }
+}
+
+// A pass of at most BIN_SMALL samples in one workgroup: an LDS hash table of the keys gives
+// each sample its rank within its anchor, a scan over the slots the first record and work
+// item of each anchor, and the records and items follow.  (Anchors come in slot order, not
+// key order.)  The seven kernels of the general path cost a launch each, which is all that
+// such a pass takes (1950 samples at lmax 256, interpolation with kmax 8: 66 us
+// through the general path, 18 us, 9 of them here).
+constexpr int SMALL_NT = 1024;
+constexpr int SMALL_SPT = BIN_SMALL / SMALL_NT;
+constexpr int SMALL_HT = 2 * BIN_SMALL;  // slots: at most half of them used, so every probe ends
+constexpr int SMALL_HPT = SMALL_HT / SMALL_NT;
+
+__global__ void __launch_bounds__(SMALL_NT)
+k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, const float *__restrict__ y,
+            int4 *__restrict__ items, int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
+    __shared__ int hkey[SMALL_HT];
+    __shared__ int hcnt[SMALL_HT];  // samples of the slot's key, then its first record
+    __shared__ unsigned sh[SMALL_NT / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+#pragma unroll
+    for (int i = 0; i < SMALL_HPT; ++i) {
+        hkey[tid + i * SMALL_NT] = KEYS_EMPTY;
+        hcnt[tid + i * SMALL_NT] = 0;
+    }
+    double fu[SMALL_SPT], fv[SMALL_SPT], psi[SMALL_SPT];
+    int key[SMALL_SPT], slot[SMALL_SPT], rank[SMALL_SPT];
+#pragma unroll
+    for (int q = 0; q < SMALL_SPT; ++q) {
+        const int s = tid + q * SMALL_NT;
+        key[q] = -1;
+        if (s < n) {
+            int r0, c0;
+            anchor_of(ptg, s, g, r0, c0, fu[q], fv[q], psi[q]);
+            key[q] = r0 * g.nkc + c0;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SMALL_SPT; ++q) {
+        const int k = key[q];
+        if (k < 0) continue;
+        int h = (int)(((unsigned)k * 2654435761u) >> 19) & (SMALL_HT - 1);
+        for (;;) {  // ends: the table has more slots than keys
+            int cur = hkey[h];
+            if (cur == KEYS_EMPTY) cur = atomicCAS(&hkey[h], KEYS_EMPTY, k);
+            if (cur == KEYS_EMPTY || cur == k) break;
+            h = (h + 1) & (SMALL_HT - 1);
+        }
+        slot[q] = h;
+        rank[q] = atomicAdd(&hcnt[h], 1);
+    }
+    __syncthreads();
+    // exclusive scan over the slots of (items << 16 | samples); both stay below 2^13
+    unsigned v[SMALL_HPT], sum = 0;
+#pragma unroll
+    for (int i = 0; i < SMALL_HPT; ++i) {
+        const int c = hcnt[SMALL_HPT * tid + i];
+        v[i] = ((unsigned)((c + chunk - 1) / chunk) << 16) | (unsigned)c;
+        sum += v[i];
+    }
+    unsigned incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
+    if (lane == 63) sh[wv] = incl;
+    __syncthreads();
+    unsigned run = incl - sum;
+    for (int w = 0; w < wv; ++w) run += sh[w];
+#pragma unroll
+    for (int i = 0; i < SMALL_HPT; ++i) {
+        const int c = (int)(v[i] & 0xffff), first = (int)(run & 0xffff), it = (int)(run >> 16);
+        if (c) {
+            const int k = hkey[SMALL_HPT * tid + i];
+            hcnt[SMALL_HPT * tid + i] = first;
+            for (int q = 0; q * chunk < c; ++q)
+                items[shortn > 0 ? cap - 1 - (it + q) : it + q] =
+                    make_int4(k, first + q * chunk, c - q * chunk < chunk ? c - q * chunk : chunk, 0);
+        }
+        run += v[i];
+    }
+    if (tid == SMALL_NT - 1) {
+        const int nit = (int)(run >> 16);
+        totals[0] = n;
+        totals[1] = shortn > 0 ? 0 : nit;
+        totals[2] = 0;
+        totals[3] = shortn > 0 ? nit : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < SMALL_SPT; ++q) {
+        if (key[q] < 0) continue;
+        const RecWords rw = make_rec(fu[q], fv[q], psi[q], tid + q * SMALL_NT, y);
+        double2 *dst = (double2 *)(out.rec + hcnt[slot[q]] + rank[q]);
+        dst[0] = make_double2(rw.w[0], rw.w[1]);
+        dst[1] = make_double2(rw.w[2], rw.w[3]);
     }
 }
 
@@ -313,7 +431,7 @@ hipError_t sc_launch_count_nonfinite(const void *x, int64_t n, int f32, int *cou
     return hipGetLastError();
 }
 
-hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y, bool scatter64) {
+hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y, BinUse use) {
     BinWork &w = p->bw;
     w.last_n = n;
     const BinGeom g = sc_bin_geom(p);
@@ -321,19 +439,27 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     const int bs = 256;
     const unsigned gs = (unsigned)((n + bs - 1) / bs);
     int chunk = p->bin_chunk;
-    if (p->prec == SC_FP64) chunk = std::min(chunk, scatter64 ? BIN_CHUNK_SC64 : BIN_CHUNK_64);
+    if (p->prec == SC_FP64) chunk = std::min(chunk, use == SC_BIN_SCATTER ? BIN_CHUNK_SC64 : BIN_CHUNK_64);
+    const int shortn = use == SC_BIN_GATHER && sc_short_items(p, n) ? BIN_SHORT : 0;
+    // (the deterministic scatter reads the per-anchor tables of the general path)
+    w.small = n <= BIN_SMALL && !(use == SC_BIN_SCATTER && p->det_adjoint);
+    if (w.small) {
+        hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg, (int)n, g, w.sorted, y, w.items,
+                           shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap, w.totals);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
     const int spt = n >= (1 << 19) ? 16 : n >= (1 << 17) ? 4 : 1;
     const unsigned gk = (unsigned)((n + KEYS_NT * spt - 1) / (KEYS_NT * spt));
     auto keys = spt == 16 ? k_bin_keys<16> : spt == 4 ? k_bin_keys<4> : k_bin_keys<1>;
     hipLaunchKernelGGL(keys, dim3(gk), dim3(KEYS_NT), 0, p->stream, ptg, n, g, w.key, w.rank, w.count);
     const int nblk = (int)((nkeys + SCAN_BLOCK - 1) / SCAN_BLOCK);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, chunk);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, chunk, shortn);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_NT), 0, p->stream, w.sums, nblk, w.totals);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, w.offs,
-                       chunk);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, w.offs, chunk,
+                       shortn);
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
     hipLaunchKernelGGL(k_bin_items, dim3((unsigned)((nkeys + bs - 1) / bs)), dim3(bs), 0, p->stream, w.count,
-                       w.offs, nkeys, w.items, chunk);
+                       w.offs, nkeys, w.items, chunk, shortn, w.cap, w.totals);
     return hipGetLastError();
 }

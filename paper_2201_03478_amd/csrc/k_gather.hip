@@ -12,6 +12,8 @@
 // by up to 2.4e-7 rad); psi is reduced in FP64 before its multiples are taken.
 //
 // v1 layout: one wave per sample, lanes over components.
+#include <algorithm>
+
 #include "sc_common.h"
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -863,6 +865,157 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
     }
 }
 
+// Short items (at most BIN_SHORT = 16 samples: uniform pointings, rarely revisited cells,
+// whole calls of a few thousand samples), one wave each, no LDS and no barriers.  The
+// result is that of gather_split_item bit for bit: the same block scale, operand split,
+// products in the same order and k-sum.  A lane loads its own A operand, the eight columns
+// of component r of tile ct in map row 4 kh + g, straight from the tiled maps; the block
+// is read twice (for its maximum, then tile by tile from the highest down, each ending in
+// its Horner step), so nothing depends on the tile count.  The workgroup form pays for 128
+// samples and half a dozen barriers whatever the item holds: 1e6 uniform pointings at lmax
+// 256, kmax 2 (4e5 items) took 3.01 ms with it and take 0.99 ms, 2e5 at kmax 8 1.64 and
+// 0.59 ms (interpolation with the binning).  What bounds it is the vector work of the
+// split, some 150 instructions per tile and wave, and the latency of the two reads.
+__global__ void __launch_bounds__(256) k_gather_short(GatherDet D, int64_t cap) {
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, grp = lane >> 4;
+    const int nitems = D.totals[3];
+    const int NC4 = D.ncp >> 2, nct = (D.ncomp + 15) >> 4;
+    const int ntile = sc_map_ntile(D.cols);
+    const float nbl = -D.beta * 1.44269504088896341f;  // -beta log2(e)
+    unsigned vo[2];  // the lane's byte offset: its map row of each tap half, its component
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+        vo[kh] = (unsigned)(4 * kh + grp) * (unsigned)(ntile * NC4 * 128) + (unsigned)((r >> 2) * 128 + (r & 3) * 4);
+    const int nw = gridDim.x * 4;
+    for (int it = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv; it < nitems; it += nw) {
+        const int4 item = D.items[cap - 1 - it];
+        const int row0 = item.x / D.nkc, col0 = item.x - (item.x / D.nkc) * D.nkc;
+        const int ns = item.z, cm8 = col0 & 7;
+        double ps = 0.0;
+        float fu = 0.f, fv = 0.f;
+        int idx = -1;
+        if (r < ns) {
+            const BinRec q = D.srt.rec[item.y + r];
+            fu = (float)q.fu;
+            fv = (float)q.fv;
+            ps = q.psi;
+            idx = q.idx;
+        }
+        // Map row 4 kh + grp, column col0 + j, component 16 ct + r of the block: a wave-uniform
+        // base (row0, col0 + j, tile ct) plus the lane's offset.
+        const char *blk = (const char *)(D.maps + sc_tile_off(row0, col0, 0, ntile, NC4));
+        const int cross = 128 * (NC4 - 1);  // columns past the tile's end
+        auto load = [&](float (&v)[2][8], int ct) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const char *b = blk + 512 * ct + 16 * j + (cm8 + j >= 8 ? cross : 0);
+#pragma unroll
+                for (int kh = 0; kh < 2; ++kh) v[kh][j] = *(const float *)(b + vo[kh]);
+            }
+        };
+        float m = 0.f;
+        for (int ct = 0; ct < nct; ++ct) {
+            float v[2][8];
+            load(v, ct);
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(v[kh][j]));
+        }
+
+        // weights: a lane forms its two theta rows and two of the sample's phi columns
+        float wt[2], wf[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            wt[i] = r < ns ? es_weight_f32((fu + (float)(3 - (4 * i + grp))) * 0.25f, nbl) : 0.f;
+            wf[i] = r < ns ? es_weight_f32((fv + (float)(3 - (2 * grp + i))) * 0.25f, nbl) : 0.f;
+        }
+        float wph[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) wph[j] = __shfl(wf[j & 1], r + 16 * (j >> 1)) * SPLIT_WSCALE;
+        half8 bh[2], bl[2];
+        long b8[2];
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh) {
+            float w8[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float x = as_is(wt[kh] * wph[j]);
+                bh[kh][j] = (_Float16)x;
+                bl[kh][j] = (_Float16)(x - (float)bh[kh][j]);
+                w8[j] = x * (1.f / SPLIT_RSCALE);
+            }
+            b8[kh] = pack_fp8x8(w8);
+        }
+        double sn, cs;
+        sincos(ps, &sn, &cs);
+        const double2 e1 = make_double2(cs, sn);
+        const double2 e2 = cmul(e1, e1), e4 = cmul(e2, e2);
+        const double2 e8 = cmul(e4, e4);
+        const double2 z0 = grp == 0 ? make_double2(1.0, 0.0) : grp == 1 ? e2 : grp == 2 ? e4 : cmul(e4, e2);
+        double2 q = make_double2(0.0, 0.0);
+
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+        int e;
+        (void)frexpf(m, &e);  // block maximum < 2^e
+        const float ms = ldexpf(1.f, 15 - e);
+        const float oscale = ldexpf(1.f, e - 15) * (1.f / SPLIT_WSCALE);
+        float v[2][8];
+        load(v, nct - 1);
+        for (int ct = nct - 1; ct >= 0; --ct) {
+            float nv[2][8];
+            load(nv, ct > 0 ? ct - 1 : 0);  // the next tile's values, in flight during this one's products
+            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh) {
+                half8 ah, al;
+                float rm[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float x = as_is(v[kh][j] * ms);  // exact (power of two)
+                    ah[j] = (_Float16)x;
+                    const float r1 = as_is(x - (float)ah[j]);  // exact
+                    al[j] = (_Float16)r1;
+                    rm[j] = (r1 - (float)al[j]) * SPLIT_RSCALE;  // exact; <= 2 significant bits
+                }
+                const long ar = pack_fp8x8(rm);
+                __builtin_amdgcn_sched_barrier(0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ar, b8[kh], acc, 0, 0, 0);
+                // An FP16 product right behind the FP8 product that wrote its accumulator reads
+                // it too early (and the other way round): wait in between.  In gather_split_item
+                // the other sample tile's product stands there.
+                asm volatile("s_nop 15" : "+v"(acc));
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bl[kh], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh[kh], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl[kh], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh[kh], acc, 0, 0, 0);
+                asm volatile("s_nop 15" : "+v"(acc) : "v"(ah), "v"(al), "v"(ar), "v"(bh[kh]), "v"(bl[kh]), "v"(b8[kh]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int c0 = 16 * ct + 4 * grp;
+            double ax = (double)acc[0], ay = -(double)acc[1], bx = (double)acc[2], by = -(double)acc[3];
+            if (c0 >= D.ncomp) ax = ay = 0.0;
+            if (c0 + 2 >= D.ncomp) bx = by = 0.0;
+            const double cx = fma(bx, e1.x, fma(-by, e1.y, ax));
+            const double cy = fma(bx, e1.y, fma(by, e1.x, ay));
+            const double qx = fma(q.x, e8.x, fma(-q.y, e8.y, cx));
+            const double qy = fma(q.x, e8.y, fma(q.y, e8.x, cy));
+            q = make_double2(qx, qy);
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[kh][j] = nv[kh][j];
+        }
+        double part = z0.x * q.x - z0.y * q.y;
+        part += __shfl_xor(part, 16);
+        part += __shfl_xor(part, 32);
+        if (grp == 0 && r < ns) D.tod[idx] = (float)part * oscale;
+    }
+}
+
 template <int CT, int NWV, int MM, bool SLIDE = false>
 __device__ __forceinline__ void gather_item(const GatherDet &D, const int4 item, double *smem_d, unsigned *smax,
                                             SlideLds *sl = nullptr, bool reuse = false) {
@@ -1023,7 +1176,17 @@ hipError_t launch_mfma_w(sc_plan *p, void *tod) {
 // The split form always runs 4-wave workgroups (its 8-wave build, limited to 128
 // registers per lane, spills heavily and is not used).
 hipError_t launch_mfma_any(sc_plan *p, void *tod) {
-    if (p->gather_mma == SC_MMA_SPLIT16) return launch_mfma_w<4, SC_MMA_SPLIT16>(p, tod);
+    if (p->gather_mma == SC_MMA_SPLIT16) {
+        if (!p->bw.small) {
+            const hipError_t e = launch_mfma_w<4, SC_MMA_SPLIT16>(p, tod);
+            if (e != hipSuccess) return e;
+        }
+        if (!sc_short_items(p, p->bw.last_n)) return hipSuccess;
+        int grid = sc_persistent_grid((const void *)k_gather_short, 256, 0, 0);
+        grid = (int)std::min<int64_t>(grid, (p->bw.last_n + 3) / 4);
+        hipLaunchKernelGGL(k_gather_short, dim3(grid), dim3(256), 0, p->stream, sc_gather_det(p, tod), p->bw.cap);
+        return hipGetLastError();
+    }
     return p->gather_waves == 8 ? launch_mfma_w<8, SC_MMA_FP32>(p, tod) : launch_mfma_w<4, SC_MMA_FP32>(p, tod);
 }
 }  // namespace

@@ -505,7 +505,6 @@ __global__ void __launch_bounds__(256)
 k_scatter_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals, const BinRec *__restrict__ rec,
                  const double *__restrict__ y, double *__restrict__ gmaps, int cols, int ncp, int ncomp, int nkc,
                  double beta) {
-    using C = Sc64<W>;
     extern __shared__ __attribute__((aligned(16))) double smem_d[];
     double2 *E1 = (double2 *)smem_d;         // [S64] e^{i psi}
     double *Ys = (double *)(E1 + S64);       // [S64]

@@ -885,7 +885,7 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
                 const int64_t cnt = n - off < cur ? n - off : cur;
                 slot = timing_begin(p, SC_STAGE_BIN);
                 // the records carry the pass's TOD gradient (binned scatter: FP32 forms only)
-                e = sc_launch_binning(p, ptg + 3 * off, cnt, (const float *)tod_grad + off);
+                e = sc_launch_binning(p, ptg + 3 * off, cnt, (const float *)tod_grad + off, SC_BIN_SCATTER);
                 timing_end(p, slot);
                 if (e != hipSuccess) return hip_fail(e, "binning launch");
                 if (p->det_adjoint) {
@@ -934,7 +934,7 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
                 for (int64_t off = 0; off < n; off += pass) {
                     const int64_t cnt = n - off < pass ? n - off : pass;
                     slot = timing_begin(p, SC_STAGE_BIN);
-                    e = sc_launch_binning(p, ptg + 3 * off, cnt, nullptr, true);
+                    e = sc_launch_binning(p, ptg + 3 * off, cnt, nullptr, SC_BIN_SCATTER);
                     timing_end(p, slot);
                     if (e != hipSuccess) return hip_fail(e, "binning launch");
                     slot = timing_begin(p, SC_STAGE_SCATTER);
@@ -1227,7 +1227,7 @@ hipError_t batch_enqueue(sc_batch *b, const double *alm, hipStream_t s, bool tim
         }
         if (e == hipSuccess) {
             slot = tb(p, SC_STAGE_BIN);
-            e = D.n > 0 ? sc_launch_binning(p, D.ptg, D.n) : sc_launch_zero(p->bw.totals, 4 * sizeof(int), p->stream);
+            e = D.n > 0 ? sc_launch_binning(p, D.ptg, D.n, nullptr, SC_BIN_BATCH) : sc_launch_zero(p->bw.totals, 4 * sizeof(int), p->stream);
             timing_end(p, slot);
         }
     }

@@ -44,6 +44,11 @@ struct FftPlan {
 #define BIN_CHUNK_SC64 128
 #define BIN_PASS_MAX (1 << 27)
 
+// Passes of at most this many samples are binned by one workgroup (one launch).
+#define BIN_SMALL 4096
+// Items of at most this many samples go to the wave-per-item split gather.
+#define BIN_SHORT 16
+
 // Anchor grid of the binned gather: key = row0 * nkc + col0.
 struct BinGeom {
     double inv_hth, inv_hph;
@@ -91,10 +96,11 @@ struct BinWork {
     int *count;       // [nkeys] samples per anchor
     int2 *offs;       // [nkeys] exclusive scan of (samples, items)
     int2 *sums;       // [scan blocks]
-    int *totals;      // [4] samples, items, work cursor
+    int *totals;      // [4] samples, items, work cursor, short items (deterministic mode: largest item)
     int *key, *rank;  // [cap]
     BinSorted sorted; // [cap]
-    int4 *items;      // [cap] (key, first sorted sample, count, -)
+    int4 *items;      // [cap] (key, first sorted sample, count, -); short items from the end down
+    int small;        // the most recent pass was binned by one workgroup (n <= BIN_SMALL)
     int64_t last_n;   // samples of the most recent binning pass
     size_t bytes;
 };
@@ -258,8 +264,10 @@ hipError_t sc_launch_count_nonfinite(const void *x, int64_t n, int f32, int *cou
 hipError_t sc_launch_gather(sc_plan *p, const double *ptg, int64_t n, void *tod);
 // Sort samples into anchor order (k_bin.hip).  With y (FP32 adjoint passes) the
 // records take the adjoint layout AdjRec instead of BinRec.
-// scatter64: items of the FP64 scatter instead of the gather's.
-hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y = nullptr, bool scatter64 = false);
+// use: who reads the work items (their size, and whether short ones are listed apart).
+enum BinUse { SC_BIN_GATHER, SC_BIN_BATCH, SC_BIN_SCATTER };
+hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const float *y = nullptr,
+                             BinUse use = SC_BIN_GATHER);
 hipError_t sc_launch_dipole(const double *blm, int lmax, int kmax, const double *ptg, int64_t n, const double *beta,
                             int64_t spp, double T0, double q, double *out, hipStream_t stream);
 hipError_t sc_launch_gather_binned(sc_plan *p, void *tod);
@@ -269,6 +277,16 @@ GatherDet sc_gather_det(const sc_plan *p, void *tod);
 hipError_t sc_launch_gather_batch(const GatherDet *dets_dev, int ndet, int max_ct, int *cursor, int wgs_per_cu, int waves,
                                   int mma, hipStream_t stream);
 bool sc_gather_binned_supported(const sc_plan *p);
+// Whether a gather pass of n samples lists its short items apart for k_gather_short (the
+// split form's FP32 maps).  That kernel splits the map block per wave, 16 ncomp values a
+// lane: with more than nine component tiles the workgroup form is the faster one for short
+// items too (1e5 uniform pointings at lmax 512, kmax 100: 2.25 against 2.46 ms; 2e5 at
+// lmax 256, kmax 64: 2.92 against 1.64 ms), unless the pass is too small to fill the chip
+// with workgroups (3000 scan samples at lmax 512, kmax 100: 113 against 53 us).
+static inline bool sc_short_items(const sc_plan *p, int64_t n) {
+    return p->prec != SC_FP64 && p->W == 8 && p->gather_mma == SC_MMA_SPLIT16 && !p->gather_valu &&
+           (n <= BIN_SMALL || p->ncomp <= 144);
+}
 
 static inline BinGeom sc_bin_geom(const sc_plan *p) {
     const double two_pi = 6.283185307179586477;
