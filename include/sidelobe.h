@@ -98,8 +98,8 @@ enum sc_precision {
  * Create a plan for one (lmax, kmax, precision).
  *   lmax          0 <= lmax <= SC_LMAX_MAX (8192), band limit of sky and beam.
  *                 The theta and phi transforms (about 2 lmax and 4 lmax
- *                 points) run in one workgroup's LDS up to 9216 points; above
- *                 that (lmax > 2303) each runs as several LDS transforms through
+ *                 points) run in one workgroup's LDS up to 10240 points; above
+ *                 that (lmax > 2559) each runs as several LDS transforms through
  *                 an extra (kmax + 1)(2 lmax + 1)^2 complex128 plan buffer.
  *                 Larger lmax: SC_EINVAL.
  *   kmax          0 <= kmax <= min(lmax, 127), beam azimuthal truncation

@@ -27,6 +27,7 @@
 #define SC_FFT_PT 9
 #define SC_FFT_NT_HUGE 1024
 #define SC_FFT_PT_HUGE 9
+#define SC_FFT_PT_FULL 10  // with 1024 threads: up to SC_FFT_MAX points (complex128 only)
 
 // ---------------------------------------------------------------------------
 // Compile-time cos / sin of 2 pi a / R (constants of the register sub-transforms):

@@ -455,9 +455,15 @@ hipError_t sc_launch_widen(const float2 *src, double2 *dst, size_t n, hipStream_
 }
 
 // Size class of a transform of length n: 0 = (256 threads, 9 points each),
-// 1 = (512, 9), 2 = (1024, 9); the longest supported transform is 9216 points.
+// 1 = (512, 9), 2 = (1024, 9), 3 = (1024, 10): 9217 to 10240 points, complex128 in the
+// whole LDS of a CU.  One such workgroup per CU is still faster than the split stages,
+// whose columns are transformed singly and whose stores cross XCDs (lmax 2500, kmax 4:
+// theta 20 -> 2.7 ms, phi 7.2 -> 2.9 ms).
 static inline int fft_class(int n) {
-    return n <= SC_FFT_NT * SC_FFT_PT ? 0 : n <= SC_FFT_NT_BIG * SC_FFT_PT ? 1 : 2;
+    return n <= SC_FFT_NT * SC_FFT_PT             ? 0
+           : n <= SC_FFT_NT_BIG * SC_FFT_PT       ? 1
+           : n <= SC_FFT_NT_HUGE * SC_FFT_PT_HUGE ? 2
+                                                  : 3;
 }
 
 template <int NT, int PT, typename S2, typename SOS, typename CT>
@@ -480,7 +486,7 @@ static hipError_t theta_up(sc_plan *p) {
     return p->mid32 ? theta_up_t<NT, PT, S2, SOS, float2>(p) : theta_up_t<NT, PT, S2, SOS, double2>(p);
 }
 
-template <typename T, int NT, int PT, typename SP = FftGeneric>
+template <typename T, int NT, int PT, typename SP = FftGeneric, bool C64 = true>
 static hipError_t phi_syn(sc_plan *p) {
     // FP32 maps with a compile-time transform: two k per workgroup (16-byte stores);
     // FP64 maps store 16 bytes per k already
@@ -488,22 +494,24 @@ static hipError_t phi_syn(sc_plan *p) {
     const int nk = p->kmax + 1;
     const int nblk = (nk + KP - 1) / KP * p->rows;
     constexpr int ntw = FftRun<1, NT, PT, SP>::ntw;
-    if (p->mid32) {
-        const size_t lds = (FftLen<SP>::value > 0 ? sizeof(float2) : sizeof(double2)) * (size_t)p->nphi +
-                           sizeof(double2) * ntw;
-        auto kern = k_phi_synthesis<T, NT, PT, SP, KP, float2>;
-        hipError_t e = sc_set_lds_attr((const void *)kern, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), lds, p->stream, (const float2 *)p->G, (T *)p->maps, p->lmax,
-                           p->rows, p->gst, p->cols, p->ncp, p->W, nk, p->pphi, p->twphi);
-    } else {
-        const size_t lds = sizeof(double2) * ((size_t)p->nphi + ntw);
-        auto kern = k_phi_synthesis<T, NT, PT, SP, KP, double2>;
-        hipError_t e = sc_set_lds_attr((const void *)kern, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), lds, p->stream, (const double2 *)p->G, (T *)p->maps, p->lmax,
-                           p->rows, p->gst, p->cols, p->ncp, p->W, nk, p->pphi, p->twphi);
+    if constexpr (C64) {
+        if (p->mid32) {
+            const size_t lds = (FftLen<SP>::value > 0 ? sizeof(float2) : sizeof(double2)) * (size_t)p->nphi +
+                               sizeof(double2) * ntw;
+            auto kern = k_phi_synthesis<T, NT, PT, SP, KP, float2>;
+            hipError_t e = sc_set_lds_attr((const void *)kern, lds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), lds, p->stream, (const float2 *)p->G, (T *)p->maps, p->lmax,
+                               p->rows, p->gst, p->cols, p->ncp, p->W, nk, p->pphi, p->twphi);
+            return hipGetLastError();
+        }
     }
+    const size_t lds = sizeof(double2) * ((size_t)p->nphi + ntw);
+    auto kern = k_phi_synthesis<T, NT, PT, SP, KP, double2>;
+    hipError_t e = sc_set_lds_attr((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), lds, p->stream, (const double2 *)p->G, (T *)p->maps, p->lmax,
+                       p->rows, p->gst, p->cols, p->ncp, p->W, nk, p->pphi, p->twphi);
     return hipGetLastError();
 }
 
@@ -563,7 +571,8 @@ hipError_t sc_launch_theta_upsample(sc_plan *p) {
     switch (fft_class(p->n2os)) {
         case 0: return theta_up<SC_FFT_NT, SC_FFT_PT>(p);
         case 1: return theta_up<SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        default: return theta_up<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 2: return theta_up<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        default: return theta_up_t<SC_FFT_NT_HUGE, SC_FFT_PT_FULL, FftGeneric, FftGeneric, double2>(p);
     }
 }
 
@@ -575,7 +584,8 @@ static hipError_t phi_syn_any(sc_plan *p) {
     switch (fft_class(p->nphi)) {
         case 0: return phi_syn<T, SC_FFT_NT, SC_FFT_PT>(p);
         case 1: return phi_syn<T, SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        default: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 2: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        default: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_FULL, FftGeneric, false>(p);
     }
 }
 
@@ -589,7 +599,8 @@ static hipError_t phi_adj_any(sc_plan *p, const void *gmaps) {
     switch (fft_class(p->nphi)) {
         case 0: return phi_adj<T, SC_FFT_NT, SC_FFT_PT>(p, gmaps);
         case 1: return phi_adj<T, SC_FFT_NT_BIG, SC_FFT_PT>(p, gmaps);
-        default: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p, gmaps);
+        case 2: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p, gmaps);
+        default: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_FULL>(p, gmaps);
     }
 }
 
@@ -616,6 +627,7 @@ hipError_t sc_launch_theta_adjoint(sc_plan *p) {
     switch (fft_class(p->n2os)) {
         case 0: return theta_adj<SC_FFT_NT, SC_FFT_PT>(p);
         case 1: return theta_adj<SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        default: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 2: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        default: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_FULL>(p);
     }
 }

@@ -1,5 +1,5 @@
 // k_fft_big.hip -- theta upsampling and phi synthesis (and their adjoints) for
-// band limits whose transforms exceed one workgroup's LDS (more than 9216 points).
+// band limits whose transforms exceed one workgroup's LDS (more than 10240 points).
 //
 // The stages compute what k_fft.hip computes (same grids, kernel deconvolution and
 // component layout; Galloway et al. 2022, Sec. 2.1), one theta column or one

@@ -83,7 +83,7 @@ static int radix_passes(int a, int b, int c, int *out) {
 bool factor_fft(int n, FftPlan *P) {
     P->n = n;
     P->nst = 0;
-    if (n < 2 || n > 1024 * 9) return false;  // longest LDS transform: 1024 threads x 9 points
+    if (n < 2 || n > SC_FFT_MAX) return false;  // longest LDS transform: 1024 threads x 10 points
     int m = n, a = 0, b = 0, c = 0;
     while (m % 2 == 0) { m /= 2; ++a; }
     while (m % 3 == 0) { m /= 3; ++b; }
@@ -116,11 +116,11 @@ bool factor_fft(int n, FftPlan *P) {
     return true;
 }
 
-// A transform of length n as P sub-transforms of length n / P that fit one workgroup
-// (smallest such P <= 16; P = 1 when the whole transform fits).
-bool split_fft(int n, int *P, FftPlan *Q) {
+// A transform of length n as P sub-transforms of at most `most` points that fit one
+// workgroup (smallest such P <= 16; P = 1 when the whole transform fits).
+bool split_fft(int n, int most, int *P, FftPlan *Q) {
     for (int q = 1; q <= 16; ++q)
-        if (n % q == 0 && n / q <= 1024 * 9 && factor_fft(n / q, Q)) {
+        if (n % q == 0 && n / q <= most && factor_fft(n / q, Q)) {
             *P = q;
             return true;
         }
@@ -437,14 +437,17 @@ int sc_plan_create(sc_plan **out, int lmax, int kmax, int precision, int kernel_
     }
     sc_choose_ring_layout(p->nring, &p->rpt, &p->ngroups);
     sc_choose_ring_layout_mixed(p->nring, &p->rpt_mx, &p->ngroups_mx);
-    if (!split_fft(p->n2, &p->sp2, &p->p2) || !split_fft(p->n2os, &p->spos, &p->p2os) ||
-        !split_fft(p->nphi, &p->spphi, &p->pphi)) {
+    // whole transforms fill the LDS (160 KB) at 10240 points; the split stages hold 9216
+    const int longest = std::max(p->n2os, p->nphi);
+    const int most = longest <= SC_FFT_MAX ? SC_FFT_MAX : SC_FFT_MAX_SPLIT;
+    if (!split_fft(p->n2, most, &p->sp2, &p->p2) || !split_fft(p->n2os, most, &p->spos, &p->p2os) ||
+        !split_fft(p->nphi, most, &p->spphi, &p->pphi)) {
         delete p;
         return fail(SC_EINVAL, "lmax = %d: no transform plan for lengths %d, %d, %d", lmax, p->n2, p->n2os, p->nphi);
     }
     p->big = p->sp2 > 1 || p->spos > 1 || p->spphi > 1;
     p->spad = (2 * lmax + 1 + 63) & ~63;
-    p->mid32 = precision != SC_FP64 && !p->big;
+    p->mid32 = precision != SC_FP64 && longest <= SC_FFT_MAX_SPLIT;
     p->gst = p->mid32 ? 2 * lmax + 2 : 2 * lmax + 1;
 
     const size_t nm = 2 * (size_t)lmax + 1;

@@ -26,6 +26,11 @@
 #define SC_PLAN_2160 15, 12, 12
 #define SC_PLAN_4320 9, 5, 6, 16
 
+// Longest transform one workgroup's LDS holds in complex128 (exactly 160 KB), and the
+// longest sub-transform of the split stages (k_fft_big.hip).
+#define SC_FFT_MAX 10240
+#define SC_FFT_MAX_SPLIT 9216
+
 struct FftPlan {
     int n;
     int nst;
@@ -121,8 +126,8 @@ struct sc_plan {
     hipEvent_t ev_fork, ev_join;  // (created on first use)
     hipEvent_t ev_stream;         // orders a new stream after the old one (sc_plan_set_stream)
 
-    // Transform plans.  A transform longer than one workgroup's LDS (9216 points) runs as
-    // sp* sub-transforms of length n / sp* (k_fft_big.hip); the plans and twiddle tables
+    // Transform plans.  When a transform is longer than one workgroup's LDS (SC_FFT_MAX) they
+    // run as sp* sub-transforms of length n / sp* (k_fft_big.hip); the plans and twiddle tables
     // below are those of the (sub-)transform length, n2, n2os and nphi the full lengths.
     FftPlan p2, p2os, pphi;
     int sp2, spos, spphi;
@@ -131,7 +136,7 @@ struct sc_plan {
     int spad;          // padded row length of S (>= 2 lmax + 1)
 
     // Storage of the two spectral intermediates of the forward synthesis.  The FP32-map
-    // forms (without split transforms) hold them as complex64: every value is still
+    // forms (up to SC_FFT_MAX_SPLIT points) hold them as complex64: every value is still
     // computed in FP64 and rounded once on store, an error (2^-24 relative) of the
     // size the FP32 maps already carry, for half the bytes of the two largest
     // round trips through HBM.  The adjoint always uses them as complex128.
