@@ -20,11 +20,19 @@
 // per-l sums as R+'s:
 //     Q+(l) = sum_{j north} [d^l_mk(theta_j) F_adj(theta_j, m) + (-1)^k dt F_adj(pi - theta_j, m)],
 //     Q-(l) = sum_{j north} [d^l_mk(theta_j) F_adj(pi - theta_j, -m) + (-1)^k dt F_adj(theta_j, -m)],
-// dt = (-1)^l d^l_{-m,k}(theta_j).  The sums over rings are reductions across lanes for every l: each
-// lane adds its rings' products, writes the 4 real partials of each l to a
-// padded LDS buffer, and every 8 l the buffer is reduced by reading it
-// transposed (two lanes per (l, value) row).  One wave per ring group; the
-// waves of a workgroup are the groups of one (k, m) and are combined in LDS.
+// dt = (-1)^l d^l_{-m,k}(theta_j).  The recursion is the forward kernel's, on
+// u^l = d^l / S_l with the plan's coefficient table, and S_l multiplies the finished sums.
+//
+// The sums over rings are reductions across lanes for every l.  A lane holds up to nine
+// northern rings and adds their products, 4 real partials per l, in registers; the 64 lanes
+// then halve the partials of 16 consecutive l against each other (at every level a lane
+// keeps one of two values and adds its partner's copy of it), so that after 63 exchanges
+// each lane holds one finished (l, value) sum.  The exchanges over 32 and 16 lanes are
+// single swap instructions, those inside a row are DPP moves: about 16 instructions per l
+// and wave beside 6 FMAs per ring, no LDS round trip.  With all of the 270 northern rings of
+// lmax 512 in one wave, lmax 512, kmax 32 takes 0.84 ms, 33 TFLOP/s (2.21 ms when the
+// partials of every l went through a padded LDS buffer, 8 l at a time, three rings per lane).
+// Waves of a workgroup are the ring groups of one (k, m) and are combined in LDS.
 // Per-k contributions go to GA[k][alm index]; a second kernel sums over k in a
 // fixed order (deterministic).  Columns with more than 2048 rings are split into
 // slabs of rings, one workgroup each, whose partial sums go to separate copies of
@@ -44,22 +52,122 @@ namespace {
 
 using namespace wrec;
 
-constexpr int ADJ_FLUSH = 8;   // l steps per LDS flush
-constexpr int ADJ_ROW = 65;    // padded row length (doubles) of the partial buffer
+constexpr int ADJ_MAXR = 9;  // rings per lane
+constexpr int ADJ_MAXW = 4;  // waves per workgroup: at most 1024 northern rings
+constexpr int ADJ_GRP = 16;  // l steps per reduction
+
+__device__ __forceinline__ double dbl(int lo, int hi) { return __hiloint2double(hi, lo); }
+
+// One level of the reduction over lane pairs 32 (or 16) apart: lanes of the lower half (even
+// rows) get a's pair sum, the others b's.
+template <bool ROWS>
+__device__ __forceinline__ double fold_swap(double a, double b) {
+    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+    const unsigned al = (unsigned)__double2loint(a), ah = (unsigned)__double2hiint(a);
+    const unsigned bl = (unsigned)__double2loint(b), bh = (unsigned)__double2hiint(b);
+    uint2v l, h;
+    if constexpr (ROWS) {
+        l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+        h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    } else {
+        l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    }
+    return dbl((int)l[0], (int)h[0]) + dbl((int)l[1], (int)h[1]);
+}
+
+// One level inside a row of 16 lanes: partner lane by the DPP control (an involution that
+// flips the lane bit `hi` tells); lanes with hi = false get a's pair sum, the others b's.
+template <int CTRL>
+__device__ __forceinline__ double fold_dpp(double a, double b, bool hi) {
+    const double keep = hi ? b : a, send = hi ? a : b;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(send), CTRL, 0xf, 0xf, true);
+    const int up = __builtin_amdgcn_mov_dpp(__double2hiint(send), CTRL, 0xf, 0xf, true);
+    return keep + dbl(lo, up);
+}
+constexpr int DPP_ROR8 = 0x128;      // lane ^ 8
+constexpr int DPP_HALF_MIRROR = 0x141;  // lane ^ 7
+constexpr int DPP_XOR2 = 0x4e;       // quad_perm 2, 3, 0, 1
+constexpr int DPP_XOR1 = 0xb1;       // quad_perm 1, 0, 3, 2
+
+// The 4 partials of one l to one value per lane: rows 0 .. 3 hold values 0, 2, 1, 3.
+__device__ __forceinline__ double fold_values(const double (&p)[4]) {
+    return fold_swap<true>(fold_swap<false>(p[0], p[1]), fold_swap<false>(p[2], p[3]));
+}
+
+// Rings of one lane.
+template <int RPT>
+struct AdjRings {
+    double x[RPT], u[RPT], up[RPT];
+    double2 fa[RPT], fm[RPT];
+    int e[RPT];
+};
+
+// One l: partial sums of the lane's rings (scaled rings, e != 0, are below 2^-600 and add
+// nothing) and the recursion step.
+template <int RPT, bool MASK>
+__device__ __forceinline__ void adj_step(double a, double b, AdjRings<RPT> &R, double (&p)[4]) {
+    p[0] = p[1] = p[2] = p[3] = 0.0;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const double v = MASK && R.e[r] != 0 ? 0.0 : R.u[r];
+        p[0] = fma(v, R.fa[r].x, p[0]);
+        p[1] = fma(v, R.fa[r].y, p[1]);
+        p[2] = fma(v, R.fm[r].x, p[2]);
+        p[3] = fma(v, R.fm[r].y, p[3]);
+        const double un = fma(fma(a, R.x[r], b), R.u[r], -R.up[r]);
+        R.up[r] = R.u[r];
+        R.u[r] = un;
+    }
+}
+
+// ADJ_GRP steps; returns the lane's finished sum: value (row 0 .. 3: 0, 2, 1, 3) of step
+// b3 + 2 b2 + 4 b1 + 8 b0 for lane bits b3 .. b0.
+template <int RPT, bool MASK>
+__device__ __forceinline__ double adj_group(const double *cA, const double *cB, AdjRings<RPT> &R, int lane) {
+    double q3 = 0.0, q2 = 0.0, q1 = 0.0, q0 = 0.0;  // first halves waiting at each level
+    double res = 0.0;
+#pragma unroll
+    for (int t = 0; t < ADJ_GRP; ++t) {
+        double p[4];
+        adj_step<RPT, MASK>(cA[t], cB[t], R, p);
+        double v = fold_values(p);
+        if ((t & 1) == 0) {
+            q3 = v;
+        } else {
+            v = fold_dpp<DPP_ROR8>(q3, v, lane & 8);
+            if ((t & 2) == 0) {
+                q2 = v;
+            } else {
+                v = fold_dpp<DPP_HALF_MIRROR>(q2, v, lane & 4);
+                if ((t & 4) == 0) {
+                    q1 = v;
+                } else {
+                    v = fold_dpp<DPP_XOR2>(q1, v, lane & 2);
+                    if ((t & 8) == 0)
+                        q0 = v;
+                    else
+                        res = fold_dpp<DPP_XOR1>(q0, v, lane & 1);
+                }
+            }
+        }
+        if (t & 1) __builtin_amdgcn_sched_barrier(0);  // keep the coefficient reads near their steps
+    }
+    return res;
+}
 
 template <int RPT, bool BEAM>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(64 * ADJ_MAXW) __attribute__((amdgpu_waves_per_eu(2)))
 k_ring_sums_adjoint(const double2 *__restrict__ FA, const double2 *__restrict__ coefs, double2 *__restrict__ GA,
                     const double *__restrict__ sbin_m, const int *__restrict__ sbin_e,
-                    const double *__restrict__ rtab, int lmax, int kmax, int nring, int alm_lmax, int nslab,
-                    int per) {
+                    const double *__restrict__ rtab, const double2 *__restrict__ rroot,
+                    const double4 *__restrict__ ctab, const long long *__restrict__ ctab_off, int lmax, int kmax,
+                    int nring, int alm_lmax, int nslab, int per) {
     // coefs: the beam b_lk (sky gradient into GA[k]) or, with BEAM, the sky a_lm
     // in the alm_lmax layout (beam gradient into GA[m], blm layout)
-    extern __shared__ __attribute__((aligned(16))) double adj_smem[];
+    __shared__ double cA[64], cB[2 * 64], cS[64];
+    __shared__ double Qw[ADJ_MAXW][64][4];
     const int nw = blockDim.x >> 6;
-    double *cA = adj_smem, *cB = cA + 128, *cC = cB + 128;  // [64][2] per recursion, [64]
-    double *Qw = cC + 64;                                    // [nw][64][4]
-    double *PB = Qw + nw * 64 * 4;                                          // [nw][4][FLUSH][ROW]
     const int slab = blockIdx.x % nslab;  // rings [slab per, slab per + per)
     const int b = blockIdx.x / nslab;
     const int k = b % (kmax + 1);
@@ -81,107 +189,89 @@ k_ring_sums_adjoint(const double2 *__restrict__ FA, const double2 *__restrict__ 
     for (int l = (BEAM ? k : m) + tid; l < l0 && l <= lmax; l += blockDim.x) gk[l] = make_double2(0.0, 0.0);
     if (l0 > lmax) return;
 
-    double x[RPT], d[RPT], dp[RPT];
-    int e[RPT];
-    double2 fap[RPT], fam[RPT];
+    AdjRings<RPT> R;
     const XN pref = {sbin_m[l0 * (kmax + 1) + mn], sbin_e[l0 * (kmax + 1) + mn]};
     const double pfe = (double)pref.e, pfm = log2(pref.m);  // log2 of the start prefactor
     const double sk = (k & 1) ? -1.0 : 1.0;
+    bool scaled = false;
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
         const int jl = (w * RPT + r) * 32 + sub;  // northern ring within the slab
         const int j = slab * per + jl, js = nring - 1 - j;
-        dp[r] = 0.0;
-        fap[r] = make_double2(0.0, 0.0);
-        fam[r] = make_double2(0.0, 0.0);
+        R.up[r] = 0.0;
+        R.fa[r] = make_double2(0.0, 0.0);
+        R.fm[r] = make_double2(0.0, 0.0);
+        R.x[r] = 0.0;
+        R.u[r] = 0.0;
+        R.e[r] = 0;
         if (jl < per && j < nh && (tp == 0 || js != j)) {  // R- skips the equator ring of an odd count
-            start_value(rtab + 5 * j, m, k, pfe, pfm, x[r], d[r], e[r], tp == 1);
+            start_value(rtab + 5 * j, m, k, pfe, pfm, R.x[r], R.u[r], R.e[r], tp == 1);
             if (tp == 0) {
-                fap[r] = FA[((size_t)k * nm + (m + lmax)) * nring + j];
-                if (m > 0) fam[r] = FA[((size_t)k * nm + (lmax - m)) * nring + js];
+                R.x[r] = -R.x[r];  // y' = -y (k_synth.hip)
+                R.fa[r] = FA[((size_t)k * nm + (m + lmax)) * nring + j];
+                if (m > 0) R.fm[r] = FA[((size_t)k * nm + (lmax - m)) * nring + js];
             } else {
-                if (l0 & 1) d[r] = -d[r];  // (-1)^l d^l_{-m,k} at l = l0
-                fap[r] = cscale(FA[((size_t)k * nm + (m + lmax)) * nring + js], sk);
-                if (m > 0) fam[r] = cscale(FA[((size_t)k * nm + (lmax - m)) * nring + j], sk);
+                if (l0 & 1) R.u[r] = -R.u[r];  // (-1)^l u^l_{-m,k} at l = l0
+                R.fa[r] = cscale(FA[((size_t)k * nm + (m + lmax)) * nring + js], sk);
+                if (m > 0) R.fm[r] = cscale(FA[((size_t)k * nm + (lmax - m)) * nring + j], sk);
             }
-        } else {
-            x[r] = 0.0;
-            d[r] = 0.0;
-            e[r] = 0;
         }
+        scaled |= R.e[r] != 0;
     }
+    bool fast = !__any(scaled);
 
-    double *pbw = PB + (size_t)w * 4 * ADJ_FLUSH * ADJ_ROW;
-    const double mm = (double)m * m, kk = (double)k * k, mk = (double)m * k;
+    const double4 *ccol = ctab ? ctab + ctab_off[m * (kmax + 1) + k] : nullptr;
+    double s_prev = 1.0, s_cur = 1.0;
+    // the finished sum a lane holds after each group: value tv of step tl
+    const int tv = ((lane >> 5) & 1) | ((lane >> 3) & 2);
+    const int tl = ((lane >> 3) & 1) | ((lane >> 1) & 2) | ((lane << 1) & 4) | ((lane << 3) & 8);
     for (int lc = l0; lc <= lmax; lc += 64) {
         __syncthreads();  // previous chunk's coefficients and Qw are consumed
-        if (tid < 64 && lc + tid <= lmax) {
-            double A, B, C, Bn, Cn;
-            rec_coefs(lc + tid, mm, kk, mk, A, B, C);      // B = alpha - beta
-            rec_coefs(lc + tid, mm, kk, -mk, A, Bn, Cn);   // Bn = alpha + beta (the column (-m, k))
-            cA[2 * tid] = -A;  // R+: (alpha - beta) - alpha y
-            cB[2 * tid] = B;
-            cA[2 * tid + 1] = A;  // R- on (-1)^l d: -((alpha + beta) - alpha y)
-            cB[2 * tid + 1] = -Bn;
-            cC[tid] = C;
+        if (w == 0) {
+            // (zero past lmax: those steps' sums are not used)
+            const ChunkCoef c = ctab ? chunk_coefs_tab(ccol, lc, lane, l0, lmax)
+                                     : chunk_coefs(lc, lane, l0, lmax, m, k, rroot, s_prev, s_cur);
+            cA[lane] = c.a;
+            cB[lane] = c.b;
+            cB[64 + lane] = -c.bn;
+            cS[lane] = c.sl;
         }
         __syncthreads();
         const int nl = (lmax - lc + 1) < 64 ? (lmax - lc + 1) : 64;
-        for (int t0 = 0; t0 < nl; t0 += ADJ_FLUSH) {
-            const int t1 = t0 + ADJ_FLUSH < nl ? t0 + ADJ_FLUSH : nl;
-            for (int t = t0; t < t1; ++t) {
-                const double A = cA[2 * t + tp], B = cB[2 * t + tp], C = cC[t];
-                double p0 = 0.0, p1 = 0.0, p2 = 0.0, p3 = 0.0;
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) {
-                    const double dd = ldexp(d[r], REC_STEP * e[r]);
-                    p0 = fma(dd, fap[r].x, p0);
-                    p1 = fma(dd, fap[r].y, p1);
-                    p2 = fma(dd, fam[r].x, p2);
-                    p3 = fma(dd, fam[r].y, p3);
-                    const double dn = fma(fma(A, x[r], B), d[r], -C * dp[r]);  // x: 1 - cos theta
-                    dp[r] = d[r];
-                    d[r] = dn;
-                }
-                double *row = pbw + (t - t0) * ADJ_ROW + lane;
-                row[0 * ADJ_FLUSH * ADJ_ROW] = p0;
-                row[1 * ADJ_FLUSH * ADJ_ROW] = p1;
-                row[2 * ADJ_FLUSH * ADJ_ROW] = p2;
-                row[3 * ADJ_FLUSH * ADJ_ROW] = p3;
-            }
+        const double *cBt = cB + 64 * tp;
+        for (int t0 = 0; t0 < nl; t0 += ADJ_GRP) {
+            Qw[w][t0 + tl][tv] = fast ? adj_group<RPT, false>(cA + t0, cBt + t0, R, lane)
+                                      : adj_group<RPT, true>(cA + t0, cBt + t0, R, lane);
+            if (fast || !(t0 & ADJ_GRP)) continue;
+            // rescaling every 32 steps (k_synth.hip)
+            bool low = false;
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
-                if (fabs(d[r]) > REC_BIG) {
-                    d[r] = rec_down(d[r]);
-                    dp[r] = rec_down(dp[r]);
-                    e[r] += 1;
+                if (fabs(R.u[r]) > REC_BIG) {
+                    R.u[r] = rec_down(R.u[r]);
+                    R.up[r] = rec_down(R.up[r]);
+                    R.e[r] += 1;
                 }
+                low |= R.e[r] != 0;
             }
-            // wave-local transpose-reduce: row (v, tt) summed by lanes 2 row, 2 row + 1
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            const int rr = lane >> 1, half = lane & 1;  // rr in [0, 32): v = rr / 8, tt = rr % 8
-            const int v = rr / ADJ_FLUSH, tt = rr % ADJ_FLUSH;
-            const double *src = pbw + (v * ADJ_FLUSH + tt) * ADJ_ROW + half * 32;
-            double s = 0.0;
-#pragma unroll 8
-            for (int q = 0; q < 32; ++q) s += src[q];
-            s += __shfl_xor(s, 1);
-            if (half == 0 && t0 + tt < t1) Qw[(w * 64 + t0 + tt) * 4 + v] = s;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
+            fast = !__any(low);
         }
         __syncthreads();
         if (tid < nl) {
             const int l = lc + tid;
             double q0 = 0.0, q1 = 0.0, q2 = 0.0, q3 = 0.0;
             for (int ww = 0; ww < nw; ++ww) {
-                const double *qq = Qw + (ww * 64 + tid) * 4;
+                const double *qq = Qw[ww][tid];
                 q0 += qq[0];
                 q1 += qq[1];
                 q2 += qq[2];
                 q3 += qq[3];
             }
+            const double sl = cS[tid];
+            q0 *= sl;
+            q1 *= sl;
+            q2 *= sl;
+            q3 *= sl;
             const double sg = ((l + k + m) & 1) ? -1.0 : 1.0;
             double2 g;
             if constexpr (BEAM) {
@@ -242,61 +332,36 @@ __global__ void k_reduce_over_k(const double2 *__restrict__ GA, double2 *__restr
 
 }  // namespace
 
-// LDS bytes of an adjoint workgroup with nw waves.
-static size_t adj_lds_bytes(int nw) {
-    return sizeof(double) * (5 * 64 + (size_t)nw * 64 * 4 + (size_t)nw * 4 * ADJ_FLUSH * ADJ_ROW);
-}
-
-// Ring slabs per (k, m) column, northern rings per slab, waves per workgroup and
-// rings per lane for the adjoint: a workgroup holds at most 1024 northern rings
-// (8 waves, 32 rings per recursion and 4 per lane; its LDS fits one CU), so longer
-// columns are split into equal slabs; per slab, the fewest idle ring slots.
+// Ring slabs per (k, m) column, northern rings per slab, waves per workgroup and rings per
+// lane: a workgroup holds at most 1024 northern rings, longer columns are split into equal
+// slabs.  A wave takes up to 32 ADJ_MAXR rings (fewest waves: the reduction is per wave).
 static void adj_layout(int nring, int *rpt, int *nw, int *nslab, int *per) {
     const int nh = (nring + 1) / 2;
-    const int ns = (nh + 1023) / 1024;
-    const int pr = (nh + ns - 1) / ns;
-    int best_r = 4, best_w = (pr + 127) / 128, best_waste = 1 << 30;
-    for (int r = 4; r >= 1; --r) {
-        const int waves = (pr + 32 * r - 1) / (32 * r);
-        if (waves > 8 || adj_lds_bytes(waves) > 160 * 1024) continue;
-        const int waste = waves * 32 * r - pr;
-        if (waste < best_waste) {
-            best_waste = waste;
-            best_r = r;
-            best_w = waves;
-        }
-    }
-    *rpt = best_r;
-    *nw = best_w;
-    *nslab = ns;
-    *per = pr;
+    *nslab = (nh + 1023) / 1024;
+    *per = (nh + *nslab - 1) / *nslab;
+    *nw = (*per + 32 * ADJ_MAXR - 1) / (32 * ADJ_MAXR);
+    *rpt = (*per + 32 * *nw - 1) / (32 * *nw);
 }
 
 int sc_adjoint_slabs(const sc_plan *p) { return ((p->nring + 1) / 2 + 1023) / 1024; }
 
-#define SC_ADJ_CASE(R)                                                                                       \
-    case R: {                                                                                                \
-        auto kern = beam ? k_ring_sums_adjoint<R, true> : k_ring_sums_adjoint<R, false>;                      \
-        e = sc_set_lds_attr((const void *)kern, lds);                                                        \
-        if (e != hipSuccess) return e;                                                                       \
-        hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * nw), lds, p->stream, p->F, (const double2 *)coefs,    \
-                           out, p->sbin_m, p->sbin_e, p->rtab, p->lmax, p->kmax, p->nring, p->alm_lmax, nslab, per); \
-    } break;
+template <int RPT>
+static hipError_t launch_adj(sc_plan *p, const double *coefs, double2 *out, bool beam, int rpt, int nw, int nslab,
+                             int per) {
+    if constexpr (RPT < ADJ_MAXR)
+        if (rpt > RPT) return launch_adj<RPT + 1>(p, coefs, out, beam, rpt, nw, nslab, per);
+    const int nblk = (p->lmax + 1) * (p->kmax + 1) * nslab;
+    auto kern = beam ? k_ring_sums_adjoint<RPT, true> : k_ring_sums_adjoint<RPT, false>;
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * nw), 0, p->stream, p->F, (const double2 *)coefs, out, p->sbin_m,
+                       p->sbin_e, p->rtab, p->rroot, p->ctab, p->ctab_off, p->lmax, p->kmax, p->nring, p->alm_lmax,
+                       nslab, per);
+    return hipGetLastError();
+}
 
 static hipError_t ring_sums_adjoint(sc_plan *p, const double *coefs, double2 *out, bool beam) {
     int rpt, nw, nslab, per;
     adj_layout(p->nring, &rpt, &nw, &nslab, &per);
-    const int nblk = (p->lmax + 1) * (p->kmax + 1) * nslab;
-    const size_t lds = adj_lds_bytes(nw);
-    hipError_t e = hipSuccess;
-    switch (rpt) {
-        SC_ADJ_CASE(1)
-        SC_ADJ_CASE(2)
-        SC_ADJ_CASE(3)
-        default:
-        SC_ADJ_CASE(4)
-    }
-    return hipGetLastError();
+    return launch_adj<1>(p, coefs, out, beam, rpt, nw, nslab, per);
 }
 
 hipError_t sc_launch_ring_sums_adjoint(sc_plan *p, const double *blm, double *grad) {
