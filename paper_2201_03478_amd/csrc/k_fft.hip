@@ -354,6 +354,79 @@ k_phi_adjoint(const T *__restrict__ gmaps, double2 *__restrict__ G, int lmax, in
     }
 }
 
+// With a compile-time transform the phi workgroup takes two consecutive k: one load per
+// column brings both component pairs, the second k's wait in registers during the first's
+// transform, and the twiddles come from LDS bases as in the forward kernel (lmax 512,
+// kmax 32: 0.82 -> 0.54 ms).
+template <typename T>
+struct Comp4 {
+    T x, y, z, w;
+};
+template <typename T, int NT, int PT, typename SP>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+k_phi_adjoint2(const T *__restrict__ gmaps, double2 *__restrict__ G, int lmax, int rows, int cols, int ncp, int W,
+               int nk, const double2 *__restrict__ twp) {
+    extern __shared__ double2 sbuf[];
+    const int nm = 2 * lmax + 1;
+    const int ngrp = (nk + 1) / 2;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int row = blk / ngrp;
+    const int k0 = (blk - row * ngrp) * 2;
+    const bool two = k0 + 1 < nk;
+    const int tid = threadIdx.x;
+    constexpr int np = FftLen<SP>::value;
+    const int q0 = -W / 2 + 1;
+    using Run = FftRun<-1, NT, PT, SP>;
+    double2 *A = sbuf;
+    double2 *Tw = A + np;
+    Run::load_tw(Tw, twp, tid);  // visible after the first barrier
+    // gradient of T_k from the stored components' gradients
+    auto pair = [](T a, T b, int k) {
+        return k == 0 ? make_double2((double)a, 0.0) : make_double2(2.0 * (double)a, -2.0 * (double)b);
+    };
+    const T *src = gmaps + (size_t)row * cols * ncp + 2 * k0;
+    constexpr int MAXQ = (np + NT - 1) / NT;
+    double2 second[MAXQ];
+    // columns q = 0 .. np-1 appear once at col = q - q0; the rest are wrap copies
+#pragma unroll
+    for (int i = 0; i < MAXQ; ++i) {
+        const int q = tid + i * NT;
+        if (q < np) {
+            const T *o = src + (size_t)(q - q0) * ncp;
+            const Comp4<T> c = two ? *(const Comp4<T> *)o : Comp4<T>{o[0], o[1], (T)0, (T)0};
+            A[q] = pair(c.x, c.y, k0);
+            second[i] = pair(c.z, c.w, 1);
+        }
+    }
+    auto transform_store = [&](int k) {
+        __syncthreads();
+        if (tid < W - 1) {
+            // the W - 1 wrap copies: cols [0, W/2 - 1) and [nphi + W/2 - 1, cols); distinct q
+            const int col = tid < W / 2 - 1 ? tid : np + tid;
+            const int q = col + q0;
+            const int qq = q < 0 ? q + np : q - np;
+            const T *o = src + (size_t)col * ncp + 2 * (k - k0);
+            A[qq] = cadd(A[qq], pair(o[0], o[1], k));
+        }
+        __syncthreads();
+        Run::run_l(A, Tw, tid);
+        double2 *dst = G + ((size_t)k * rows + row) * nm;
+        for (int t = tid; t < nm; t += NT) {
+            const int m = t - lmax;
+            dst[t] = A[m < 0 ? m + np : m];
+        }
+    };
+    transform_store(k0);
+    if (!two) return;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MAXQ; ++i) {
+        const int q = tid + i * NT;
+        if (q < np) A[q] = second[i];
+    }
+    transform_store(k0 + 1);
+}
+
 // Two columns per workgroup, as in the forward kernel.  The forward output lies
 // in the s-symmetric sequences (G(-r) = s G(r)), so the adjoint only sees the
 // symmetric part of the row gradient: with A_c the gradient placed on the circle
@@ -378,6 +451,15 @@ k_theta_adjoint(const double2 *__restrict__ G, double2 *__restrict__ F, int lmax
     const int tid = threadIdx.x, nth = blockDim.x;
     const int n2 = P2.n, nos = Pos.n;
     double2 *B = sbuf;  // length nos; the length-n2 transform runs in B[0 .. n2)
+    // compile-time transforms: twiddle bases in LDS, as in the forward kernel
+    constexpr bool TWL = FftLen<S2>::value > 0 && FftLen<SOS>::value > 0;
+    using Fwd = FftRun<-1, NT, PT, SOS>;
+    using Inv = FftRun<1, NT, PT, S2>;
+    double2 *Tf = B + nos, *Ti = Tf + Fwd::ntw;
+    if constexpr (TWL) {
+        Fwd::load_tw(Tf, twos, tid);
+        Inv::load_tw(Ti, tw2, tid);  // visible after the fill's barrier
+    }
     const double s1 = ((m - k) & 1) ? -1.0 : 1.0;
     const int r0 = -W / 2 + 1;
     const int rtop = r0 + rows - 1;  // last kept row index (< nos / 2 + W)
@@ -403,7 +485,10 @@ k_theta_adjoint(const double2 *__restrict__ G, double2 *__restrict__ F, int lmax
         B[r] = make_double2(u.x - v.y, u.y + v.x);
     }
     __syncthreads();
-    FftRun<-1, NT, PT, SOS>::run(B, Pos, twos, tid, nth);
+    if constexpr (TWL)
+        Fwd::run_l(B, Tf, tid);
+    else
+        Fwd::run(B, Pos, twos, tid, nth);
     // Coefficients n in [-lmax, lmax]: n >= 0 stay at n, n < 0 move from n + nos to
     // n + n2 (disjoint since nos >= n2 + lmax); the rest of [0, n2) becomes zero.
     constexpr int MAXC = (PT + 1) / 2;
@@ -432,7 +517,10 @@ k_theta_adjoint(const double2 *__restrict__ G, double2 *__restrict__ F, int lmax
     }
     for (int t = lmax + 1 + tid; t < n2 - lmax; t += nth) B[t] = zero;
     __syncthreads();
-    FftRun<1, NT, PT, S2>::run(B, P2, tw2, tid, nth);
+    if constexpr (TWL)
+        Inv::run_l(B, Ti, tid);
+    else
+        Inv::run(B, P2, tw2, tid, nth);
     double2 *col = F + ((size_t)k * nm + mi) * nring;
     for (int j = tid; j < nring; j += nth) {
         const double2 a = B[j], b = B[n2 - 1 - j];
@@ -544,10 +632,24 @@ static hipError_t phi_adj(sc_plan *p, const void *gmaps) {
     return hipGetLastError();
 }
 
+template <typename T, int NT, int PT, typename SP>
+static hipError_t phi_adj2(sc_plan *p, const void *gmaps) {
+    const int nk = p->kmax + 1;
+    const int nblk = (nk + 1) / 2 * p->rows;
+    const size_t lds = sizeof(double2) * ((size_t)p->nphi + FftRun<-1, NT, PT, SP>::ntw);
+    auto kern = k_phi_adjoint2<T, NT, PT, SP>;
+    hipError_t e = sc_set_lds_attr((const void *)kern, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), lds, p->stream, (const T *)gmaps, p->G, p->lmax, p->rows, p->cols,
+                       p->ncp, p->W, nk, p->twphi);
+    return hipGetLastError();
+}
+
 template <int NT, int PT, typename S2 = FftGeneric, typename SOS = FftGeneric>
 static hipError_t theta_adj(sc_plan *p) {
     const int nblk = (p->kmax + 1) * (p->lmax + 1);  // column pairs
-    const size_t lds = sizeof(double2) * (size_t)p->n2os;
+    constexpr int ntw = FftRun<1, NT, PT, S2>::ntw + FftRun<-1, NT, PT, SOS>::ntw;
+    const size_t lds = sizeof(double2) * ((size_t)p->n2os + ntw);
     auto kern = k_theta_adjoint<NT, PT, S2, SOS>;
     hipError_t e = sc_set_lds_attr((const void *)kern, lds);
     if (e != hipSuccess) return e;
@@ -596,6 +698,9 @@ hipError_t sc_launch_phi_synthesis(sc_plan *p) {
 
 template <typename T>
 static hipError_t phi_adj_any(sc_plan *p, const void *gmaps) {
+    if (p->nphi == 1080) return phi_adj2<T, 128, 9, F1080>(p, gmaps);
+    if (p->nphi == 2160) return phi_adj2<T, SC_FFT_NT, SC_FFT_PT, F2160>(p, gmaps);
+    if (p->nphi == 4320) return phi_adj2<T, SC_FFT_NT_BIG, SC_FFT_PT, F4320>(p, gmaps);
     switch (fft_class(p->nphi)) {
         case 0: return phi_adj<T, SC_FFT_NT, SC_FFT_PT>(p, gmaps);
         case 1: return phi_adj<T, SC_FFT_NT_BIG, SC_FFT_PT>(p, gmaps);
