@@ -346,8 +346,11 @@ __device__ __forceinline__ void fft_passes_c(double2 *buf, const double2 *__rest
 // error of a few 1e-16), so a transform needs no global loads once the bases of all
 // its passes are in LDS.  The buffer holds complex128 or complex64 values (BT); the
 // arithmetic is FP64 either way, so complex64 only rounds each pass's outputs.
-template <int R, int DIR, int NT, int N, int NS, typename BT>
-__device__ __forceinline__ void stockham_stage_l(BT *buf, const double2 *twl, int tid) {
+// BAND (first pass only): the input is zero for band < index < N - band, and those
+// elements of buf are neither read nor need be written.
+template <int R, int DIR, int NT, int N, int NS, bool BAND = false, typename BT>
+__device__ __forceinline__ void stockham_stage_l(BT *buf, const double2 *twl, int tid, int band = 0) {
+    static_assert(!BAND || NS == 1, "the band is of the transform's input");
     constexpr int nb = N / R;
     constexpr int B = (nb + NT - 1) / NT;
     double2 v[B][R];
@@ -366,7 +369,8 @@ __device__ __forceinline__ void stockham_stage_l(BT *buf, const double2 *twl, in
             }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                double2 x = ld2(buf + j + r * nb);
+                double2 x = make_double2(0.0, 0.0);
+                if (!BAND || j + r * nb <= band || j + r * nb >= N - band) x = ld2(buf + j + r * nb);
                 if (NS > 1 && r > 0) {
                     x = cmul(x, w);
                     if (r + 1 < R) w = cmul(w, w1);
@@ -392,6 +396,13 @@ template <int DIR, int NT, int N, int NS, int R, int... Rest, typename BT>
 __device__ __forceinline__ void fft_passes_l(BT *buf, const double2 *twl, int tid) {
     stockham_stage_l<R, DIR, NT, N, NS>(buf, twl, tid);
     if constexpr (sizeof...(Rest) > 0) fft_passes_l<DIR, NT, N, NS * R, Rest...>(buf, twl + (NS > 1 ? NS : 0), tid);
+}
+
+// fft_passes_l of a band-limited input (see stockham_stage_l).
+template <int DIR, int NT, int N, int R, int... Rest, typename BT>
+__device__ __forceinline__ void fft_passes_band(BT *buf, const double2 *twl, int tid, int band) {
+    stockham_stage_l<R, DIR, NT, N, 1, true>(buf, twl, tid, band);
+    if constexpr (sizeof...(Rest) > 0) fft_passes_l<DIR, NT, N, R, Rest...>(buf, twl, tid);
 }
 
 // Number of LDS base twiddles of the passes from span NS on.
@@ -442,6 +453,9 @@ struct FftRun<DIR, NT, PT, FftSpec<N, Rs...>> {
     }
     __device__ __forceinline__ static void load_tw(double2 *twl, const double2 *__restrict__ tw, int tid) {
         tw_base_load<NT, 1, Rs...>(twl, tw, tid);
+    }
+    __device__ __forceinline__ static void run_band(double2 *buf, const double2 *twl, int tid, int band) {
+        fft_passes_band<DIR, NT, N, Rs...>(buf, twl, tid, band);
     }
     // twl: the bases written by load_tw (visible to all threads); buf complex128 or complex64
     template <typename BT>

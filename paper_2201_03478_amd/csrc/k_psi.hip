@@ -32,103 +32,145 @@ constexpr int PSI_PT = 8;   // npsi <= 512
 
 constexpr int PSI_SLACK = 512;  // zeroed bytes after the cube (reached by the last pixel's quad reads)
 
-// Map values of one pixel pair at a lane's two orders k = tg, tg + NTS (tg: the lane's index
-// among the NTS lanes of its transform): (M_2k, M_2k+1) of pixel a, then of pixel b (zero past
-// kmax and for a missing b).  Two orders per lane suffice: kmax + 1 <= npsi / 4 <= 2 NTS.
+// Map values of pixels (row, c0) and (row, c0 + 1), c0 even, at a lane's two orders (tg: the
+// lane's index among the NTS lanes of its transform): (M_2k, M_2k+1) of both pixels (zero past
+// kmax and for a missing second pixel).  FP32 maps: orders 2 tg and 2 tg + 1, one 16-byte
+// group per pixel; FP64: tg and tg + NTS.  Two orders per lane suffice: kmax + 1 <= npsi / 4 <= 2 NTS.
 template <typename T, int NTS>
-__device__ __forceinline__ void fetch_pair(const T *__restrict__ maps, int64_t pair, int64_t npix, int cols, int ncp,
-                                           int kmax, int tg, T (&r)[8]) {
-    const int64_t a = 2 * pair;
-    const bool hb = a + 1 < npix;
-    // pixels are (row, column) in row-major order; rows x cols < 2^31 up to lmax 8192
-    const unsigned ua = (unsigned)a, ub = hb ? ua + 1u : ua, uc = (unsigned)cols;
-    const int ra = (int)(ua / uc), ca = (int)(ua - (unsigned)ra * uc);
-    const int rb = (int)(ub / uc), cb = (int)(ub - (unsigned)rb * uc);
+struct PairValues {
+    T v[8];
+    static __device__ __forceinline__ int order(int tg, int h) { return sizeof(T) == 4 ? 2 * tg + h : tg + NTS * h; }
+    __device__ __forceinline__ T ca(int h) const { return sizeof(T) == 4 ? v[2 * h] : v[4 * h]; }
+    __device__ __forceinline__ T sa(int h) const { return sizeof(T) == 4 ? v[2 * h + 1] : v[4 * h + 1]; }
+    __device__ __forceinline__ T cb(int h) const { return sizeof(T) == 4 ? v[4 + 2 * h] : v[4 * h + 2]; }
+    __device__ __forceinline__ T sb(int h) const { return sizeof(T) == 4 ? v[5 + 2 * h] : v[4 * h + 3]; }
+    __device__ __forceinline__ void fetch(const T *__restrict__ maps, int row, int c0, int cols, int ncp, int kmax,
+                                          int tg) {
+        const bool hb = c0 + 1 < cols;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int k = tg + NTS * h;
-        const bool ok = k <= kmax;
-        const size_t oa = sc_map_off<T>(ra, ca, ok ? 2 * k : 0, cols, ncp);
-        const size_t ob = sc_map_off<T>(rb, cb, ok ? 2 * k : 0, cols, ncp);
-        r[4 * h] = ok ? maps[oa] : (T)0;
-        r[4 * h + 1] = ok ? maps[oa + 1] : (T)0;
-        r[4 * h + 2] = ok && hb ? maps[ob] : (T)0;
-        r[4 * h + 3] = ok && hb ? maps[ob + 1] : (T)0;
+        for (int e = 0; e < 8; ++e) v[e] = (T)0;
+        if constexpr (sizeof(T) == 4) {
+            if (2 * tg > kmax) return;
+            const float4 *q = (const float4 *)(maps + sc_tile_off(row, c0, tg, sc_map_ntile(cols), ncp >> 2));
+            const float4 a = q[0];
+            v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+            if (hb) {
+                const float4 b = q[1];
+                v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = order(tg, h);
+                if (k > kmax) continue;
+                const double2 *q = (const double2 *)(maps + sc_map_off<T>(row, c0, 2 * k, cols, ncp));
+                const double2 a = q[0];
+                v[4 * h] = a.x, v[4 * h + 1] = a.y;
+                if (hb) {
+                    const double2 b = q[1];
+                    v[4 * h + 2] = b.x, v[4 * h + 3] = b.y;
+                }
+            }
+        }
     }
-}
+};
 
-// Persistent over pixel pairs, two waves per workgroup sharing the twiddle table; each wave
-// runs G transforms side by side (NTS = 64 / G lanes each, G = 1 for lengths above 128), so
-// short psi grids still fill the wave.  Iteration it of a workgroup covers pairs
-// (2 it + w) G + g for wave w and transform g.  The next pairs' map values are loaded before
-// the current transforms so that the load latency overlaps them.  Twiddles and the
-// deconvolution factors are read once per workgroup (LDS, registers): no global loads inside
-// the transform.  Every transform runs in every iteration (its barriers are the workgroup's);
-// one without a pair in the last iteration transforms stale values and stores nothing.
+// Waves of a workgroup of the psi cube kernel: a whole map tile's four pixel pairs with a
+// compile-time plan; half a tile with a runtime one, whose buffers are sized for the longest
+// transform (two waves measured faster there: 1357 against 1375 us at lmax 400, npsi 243).
+template <typename S>
+constexpr int psi_waves(int g) { return FftLen<S>::value > 0 ? 4 / g : 2; }
+
+// A workgroup takes the eight pixels of one map tile at a time (persistent over the tiles):
+// four pixel pairs, one transform each, G side by side in a wave (NTS = 64 / G lanes each,
+// G = 1 for lengths above 128), so short psi grids still fill the wave.  The tile's lines,
+// 16 bytes of each per pixel and four components, are read by waves that run together and
+// come from the vector cache after the first touch; with one pixel pair per workgroup every
+// pair pulled all of them from L2 again.  The next tile's map values are loaded before the
+// current transforms so that the load latency overlaps them.  Twiddles and the deconvolution
+// factors are read once per workgroup (LDS, registers): no global loads inside the transform.
+// A transform without a pixel (past the last column) runs on zeros and stores nothing.
+// lmax 512, kmax 100, npsi 405: 1.95 ms, against 2.10 ms with one pixel pair per two waves,
+// scalar map loads and a zeroed band; the vector units issue 75% of the time and the 4.5 GB of
+// maps and cube take 1.0 ms at the card's copy rate, so both the transforms and the stores count.
 template <typename T, typename S, int G>
-__global__ void __launch_bounds__(2 * PSI_NT)
-k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int64_t npix, int cols, int ncp, int kmax, int npsi, int npst,
+__global__ void __launch_bounds__(PSI_NT * psi_waves<S>(G))
+k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int rows, int cols, int ncp, int kmax, int npsi, int npst,
            int W, FftPlan P, const double2 *__restrict__ tw, const double *__restrict__ gpsi) {
+    constexpr int NWV = psi_waves<S>(G);
+    constexpr int PPW = NWV * G;      // pixel pairs of a workgroup's unit
     constexpr int NTS = PSI_NT / G;   // lanes per transform
     constexpr int PTS = PSI_PT * G;   // points per lane: NTS PTS = 512
     constexpr int NB = FftLen<S>::value > 0 ? FftLen<S>::value : PSI_NT * PSI_PT / G;  // LDS per transform
     static_assert(G == 1 || FftLen<S>::value > 0, "several transforms per wave need a compile-time plan");
-    __shared__ double2 bufs[2][G][NB];
-    __shared__ double2 twl[NB];
+    __shared__ double2 bufs[PPW][NB];
+    // compile-time plans: the twiddle bases of their passes; runtime plans: the whole table
+    using Run = FftRun<+1, NTS, PTS, S>;
+    constexpr bool PLAN = FftLen<S>::value > 0;
+    __shared__ double2 twl[PLAN ? Run::ntw : NB];
     const int lane = threadIdx.x & (PSI_NT - 1), wv = threadIdx.x / PSI_NT;
     const int g = lane / NTS, tg = lane - g * NTS;
-    double2 *buf = bufs[wv][g];
+    const int pr = wv * G + g;  // pixel pair of the unit
+    double2 *buf = bufs[pr];
     const int half = W / 2;
     const int ext = npsi + W - 1;
-    const int64_t npairs = (npix + 1) / 2;
-    for (int t = threadIdx.x; t < npsi; t += 2 * PSI_NT) twl[t] = tw[t];
+    const int nu = sc_map_ntile(cols) * (4 / PPW);  // units of a map row
+    const int nunit = rows * nu;
+    if constexpr (PLAN) {
+        if (pr == 0) Run::load_tw(twl, tw, tg);
+    } else {
+        for (int t = threadIdx.x; t < npsi; t += NWV * PSI_NT) twl[t] = tw[t];
+    }
     if (blockIdx.x == 0)
-        for (int e = threadIdx.x; e < PSI_SLACK / (int)sizeof(T); e += 2 * PSI_NT) cube[npix * npst + e] = (T)0;
+        for (int e = threadIdx.x; e < PSI_SLACK / (int)sizeof(T); e += NWV * PSI_NT)
+            cube[(size_t)rows * cols * npst + e] = (T)0;
+    using PV = PairValues<T, NTS>;
     double gk[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int k = tg + NTS * h;
+        const int k = PV::order(tg, h);
         gk[h] = k > kmax ? 0.0 : (k == 0 ? gpsi[0] : 0.5 * gpsi[k]);
     }
-    // consecutive pairs share the 128-byte lines of the column-tiled maps: the workgroups
-    // that take them start on one XCD (xcd_remap is a permutation of the block indices)
-    int64_t it = xcd_remap(blockIdx.x, gridDim.x);
-    T nxt[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) nxt[e] = (T)0;
-    if ((2 * it + wv) * G + g < npairs) fetch_pair<T, NTS>(maps, (2 * it + wv) * G + g, npix, cols, ncp, kmax, tg, nxt);
-    for (; 2 * it * G < npairs; it += gridDim.x) {
-        const int64_t pair = (2 * it + wv) * G + g;
-        T cur[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) cur[e] = nxt[e];
-        const int64_t pn = (2 * (it + gridDim.x) + wv) * G + g;
-        if (pn < npairs) fetch_pair<T, NTS>(maps, pn, npix, cols, ncp, kmax, tg, nxt);
-        for (int t = tg; t < npsi; t += NTS)
-            if (t > kmax && t < npsi - kmax) buf[t] = make_double2(0.0, 0.0);
+    int u = xcd_remap(blockIdx.x, gridDim.x);
+    auto fetch = [&](PV &v, int unit) {
+        const int row = unit / nu, c0 = 2 * (PPW * (unit - row * nu) + pr);
+        v.fetch(maps, row, c0 < cols ? c0 : (cols - 1) & ~1, cols, ncp, kmax, tg);
+    };
+    PV nxt;
+    if (u < nunit) fetch(nxt, u);
+    for (; u < nunit; u += gridDim.x) {
+        const int row = u / nu, c0 = 2 * (PPW * (u - row * nu) + pr);
+        const PV cur = nxt;
+        if (u + (int)gridDim.x < nunit) fetch(nxt, u + gridDim.x);
+        if constexpr (!PLAN)
+            for (int t = tg; t < npsi; t += NTS)
+                if (t > kmax && t < npsi - kmax) buf[t] = make_double2(0.0, 0.0);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int k = tg + NTS * h;
+            const int k = PV::order(tg, h);
             if (k <= kmax) {
                 const double gg = gk[h];
-                const double ca = (double)cur[4 * h], sa = (double)cur[4 * h + 1];
-                const double cb = (double)cur[4 * h + 2], sb = (double)cur[4 * h + 3];
+                const double ca = (double)cur.ca(h), sa = (double)cur.sa(h);
+                const double cb = (double)cur.cb(h), sb = (double)cur.sb(h);
                 // +k: Y_a + i Y_b with Y = g (M_2k - i M_2k+1); -k: the conjugates
                 buf[k] = make_double2(gg * (ca + sb), gg * (cb - sa));
                 if (k > 0) buf[npsi - k] = make_double2(gg * (ca - sb), gg * (cb + sa));
             }
         }
         __syncthreads();
-        FftRun<+1, NTS, PTS, S>::run(buf, P, twl, tg, NTS);
-        if (pair < npairs) {
-            const int64_t a = 2 * pair, b = a + 1;
-            const bool hb = b < npix;
+        if constexpr (PLAN)
+            Run::run_band(buf, twl, tg, kmax);  // the spectrum is zero for kmax < k < npsi - kmax
+        else
+            Run::run(buf, P, twl, tg, NTS);
+        if (c0 < cols) {
+            T *oa = cube + ((size_t)row * cols + c0) * npst;
+            const bool hb = c0 + 1 < cols;
             for (int s2 = tg; s2 < npst; s2 += NTS) {
                 int j = s2 - half + 1;
                 j = j < 0 ? j + npsi : (j >= npsi ? j - npsi : j);
                 const double2 v = s2 < ext ? buf[j] : make_double2(0.0, 0.0);
-                cube[a * npst + s2] = (T)v.x;
-                if (hb) cube[b * npst + s2] = (T)v.y;
+                oa[s2] = (T)v.x;
+                if (hb) oa[npst + s2] = (T)v.y;
             }
         }
         __syncthreads();
@@ -292,23 +334,25 @@ bool plan_is(const FftPlan &P, int n, int r0, int r1, int r2) {
 }
 
 template <typename T, typename S, int G>
-void launch_psi_cube(sc_plan *p, int64_t npix) {
-    const int64_t iters = ((npix + 1) / 2 + 2 * G - 1) / (2 * G);  // 2 G pixel pairs per workgroup iteration
-    const unsigned nblk = (unsigned)(iters < 16384 ? iters : 16384);
-    hipLaunchKernelGGL((k_psi_cube<T, S, G>), dim3(nblk), dim3(2 * PSI_NT), 0, p->stream, (const T *)p->maps,
-                       (T *)p->cube, npix, p->cols, p->ncp, p->kmax, p->npsi, p->npst, p->W, p->ppsi, p->twpsi, p->gpsi);
+void launch_psi_cube(sc_plan *p) {
+    constexpr int NWV = psi_waves<S>(G);
+    const int64_t nunit = (int64_t)p->rows * sc_map_ntile(p->cols) * (4 / (NWV * G));
+    const unsigned nblk = (unsigned)(nunit < 16384 ? nunit : 16384);
+    hipLaunchKernelGGL((k_psi_cube<T, S, G>), dim3(nblk), dim3(PSI_NT * NWV), 0, p->stream, (const T *)p->maps,
+                       (T *)p->cube, p->rows, p->cols, p->ncp, p->kmax, p->npsi, p->npst, p->W, p->ppsi, p->twpsi,
+                       p->gpsi);
 }
 
 template <typename T>
-void launch_psi_cube_any(sc_plan *p, int64_t npix) {
+void launch_psi_cube_any(sc_plan *p) {
     if (plan_is(p->ppsi, 405, 9, 9, 5))
-        launch_psi_cube<T, PsiSpec405, 1>(p, npix);
+        launch_psi_cube<T, PsiSpec405, 1>(p);
     else if (plan_is(p->ppsi, 135, 9, 15, 0))
-        launch_psi_cube<T, PsiSpec135, 2>(p, npix);
+        launch_psi_cube<T, PsiSpec135, 2>(p);
     else if (plan_is(p->ppsi, 72, 9, 8, 0))
-        launch_psi_cube<T, PsiSpec72, 4>(p, npix);
+        launch_psi_cube<T, PsiSpec72, 4>(p);
     else
-        launch_psi_cube<T, FftGeneric, 1>(p, npix);
+        launch_psi_cube<T, FftGeneric, 1>(p);
 }
 
 }  // namespace
@@ -317,11 +361,10 @@ int sc_psi_max_len() { return PSI_NT * PSI_PT; }
 int sc_psi_slack_bytes() { return PSI_SLACK; }
 
 hipError_t sc_launch_psi_cube(sc_plan *p) {
-    const int64_t npix = (int64_t)p->rows * p->cols;
     if (p->prec == SC_FP64)
-        launch_psi_cube_any<double>(p, npix);
+        launch_psi_cube_any<double>(p);
     else
-        launch_psi_cube_any<float>(p, npix);
+        launch_psi_cube_any<float>(p);
     return hipGetLastError();
 }
 
