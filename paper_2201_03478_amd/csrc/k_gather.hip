@@ -489,6 +489,16 @@ __device__ __forceinline__ void gather_mfma_item(const GatherDet &D, const int4 
 // time of the FP32 form.  The map values carry all 24 bits because their
 // rounding errors are amplified by the cancellation in the k-sum; the weight's
 // 2^-22 is not (a weight multiplies every component of its tap alike).
+// What bounds the kernel is the vector work around the products: the weights, their split
+// and the k-sum take three quarters of the issue slots, the matrix units run a quarter of
+// the time.  So the split reads its halves through mixed-precision subtractions and the
+// FP8 part through the scaled conversion (136 vector instructions a wave and chunk against
+// 230), and the weights are formed without branches, shared out against the sincos of two
+// of the waves.  With fewer registers, 3 waves a SIMD instead of 2 at 5 and 6 tiles.
+// lmax 512, kmax 32, 1e7 scan samples: 0.87 -> 0.68 ms; kmax 100: 1.47 -> 1.44 ms; lmax
+// 1024, kmax 16, 1e8 samples: 6.3 -> 5.8 ms (of which 0.6 are the scattered stores of the
+// results).  Fetching records and map values an item ahead gave nothing there (6.1 against
+// 6.1 ms) and cost registers.
 // Ranges are handled by exact power-of-two scalings: the map block of an item
 // by 2^(15 - e) with 2^e above its largest magnitude (a workgroup max taken
 // while the block is staged), the weights by 2^14 (FP16 parts) and the
@@ -524,6 +534,43 @@ __device__ __forceinline__ float as_is(float x) {
     return x;
 }
 
+// Split of eight values x into hi = fp16(x) and lo = fp16(x - hi), two at a time: one packed
+// conversion, two mixed-precision subtractions that read the halves of the packed result
+// (exact, as with the converted-back value), one packed conversion.  rem, if given, receives
+// x - hi - lo (exact).
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void sub_halves(float x0, float x1, half2v h, float &r0, float &r1) {
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(h), "v"(x0));
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(h), "v"(x1));
+}
+__device__ __forceinline__ void split_fp16x8(const float (&x)[8], half8 &hi, half8 &lo, float *rem = nullptr) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const half2v h = __builtin_convertvector((float2v{x[j], x[j + 1]}), half2v);
+        float r0, r1;
+        sub_halves(x[j], x[j + 1], h, r0, r1);
+        const half2v l = __builtin_convertvector((float2v{r0, r1}), half2v);
+        if (rem) sub_halves(r0, r1, l, rem[j], rem[j + 1]);
+        hi[j] = h[0];
+        hi[j + 1] = h[1];
+        lo[j] = l[0];
+        lo[j + 1] = l[1];
+    }
+}
+
+// eight weights x 2^-14 to eight FP8 (e4m3) bytes, element q in byte q (the scaled conversion
+// divides by its scale operand)
+typedef short short2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ long pack_fp8x8_scaled(const float (&f)[8]) {
+    short2v w0 = {0, 0}, w1 = {0, 0};
+    w0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w0, f[0], f[1], SPLIT_RSCALE, false);
+    w0 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w0, f[2], f[3], SPLIT_RSCALE, true);
+    w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, f[4], f[5], SPLIT_RSCALE, false);
+    w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, f[6], f[7], SPLIT_RSCALE, true);
+    return (long)(((unsigned long)__builtin_bit_cast(unsigned, w1) << 32) | __builtin_bit_cast(unsigned, w0));
+}
+
 // eight floats to eight FP8 (e4m3) bytes, element q in byte q
 __device__ __forceinline__ long pack_fp8x8(const float (&f)[8]) {
     int w0 = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false);
@@ -551,6 +598,7 @@ struct SlideLds {
 template <int CT, int NWV, bool SLIDE = false>
 __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4 item, double *smem_d, unsigned *smax,
                                                   SlideLds *sl = nullptr, bool reuse = false) {
+    static_assert(NWV == 4 && GCH == 128, "the weight rows below are shared out for two pairs of waves");
     constexpr int NT = 64 * NWV;
     constexpr int TPW = 8 / NWV;
     constexpr int NC = 16 * CT;
@@ -565,7 +613,7 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
     int *Idx = (int *)(E + GCH);               // [GCH]
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, grp = lane >> 4;
     const int row0 = item.x / D.nkc, col0 = item.x - (item.x / D.nkc) * D.nkc;
     // column col0 + jj of a (row, four-component group): the group's run in col0's tile,
@@ -723,15 +771,12 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
                 for (int q = 0; q < 4; ++q) {
                     const int c = 4 * c4 + q;
                     half8 hi, lo;
-                    float rm[8];
+                    float x8[8], rm[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const float x = as_is(v[k][j][q] * ms);  // exact (power of two)
-                        hi[j] = (_Float16)x;
-                        const float r1 = as_is(x - (float)hi[j]);  // exact
-                        lo[j] = (_Float16)r1;
-                        rm[j] = (r1 - (float)lo[j]) * SPLIT_RSCALE;  // exact; <= 2 significant bits
-                    }
+                    for (int j = 0; j < 8; ++j) x8[j] = as_is(v[k][j][q] * ms);  // exact (power of two)
+                    split_fp16x8(x8, hi, lo, rm);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) rm[j] *= SPLIT_RSCALE;  // exact; <= 2 significant bits
                     const int o = ((i >> 2) * CT + (c >> 4)) * 64 + (i & 3) * 16 + (c & 15);
                     Ahi[o] = hi;
                     Alo[o] = lo;
@@ -750,16 +795,26 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
     for (int ch = 0; ch < item.z; ch += GCH) {
         const int ns = item.z - ch < GCH ? item.z - ch : GCH;
         {
-            const float fu = (float)pf_u, fv = (float)pf_v;
+            // an absent sample's factors are zero: it stands outside every tap's support
+            const float fu = sw < ns ? (float)pf_u : 1e6f, fv = sw < ns ? (float)pf_v : 1e6f;
             const float nbl = -D.beta * 1.44269504088896341f;  // -beta log2(e)
             // col0 mod 8 (recomputed from the item, not held across the staging)
             const int cslot = track ? ((item.x - (item.x / D.nkc) * D.nkc) & 7) : 0;
+            auto row = [&](int q) {
+                const float w = es_weight_f32(((q < 8 ? fu : fv) + (float)(3 - (q & 7))) * 0.25f, nbl);
+                if (q < 8)
+                    W1[q * GW1 + sw] = w;
+                else  // phi factor of column col0 + j: slot row; it carries the products' scale
+                    W1[(8 + ((q + cslot) & 7)) * GW1 + sw] = w * SPLIT_WSCALE;
+            };
+            // Six of the sixteen rows for the waves that also take the samples' sincos (below,
+            // about four rows' worth), ten for the other two.
+            if (wv < 2) {
 #pragma unroll
-            for (int i = 0; i < 16 * GCH / NT; ++i) {
-                const int q = (tid >> 7) + (NT / GCH) * i;
-                float w = 0.f;
-                if (sw < ns) w = es_weight_f32(((q < 8 ? fu : fv) + (float)(3 - (q & 7))) * 0.25f, nbl);
-                W1[(track && q >= 8 ? 8 + ((q + cslot) & 7) : q) * GW1 + sw] = w;  // phi factor of column col0 + j: slot row
+                for (int q = 0; q < 6; ++q) row(q);
+            } else {
+#pragma unroll
+                for (int q = 6; q < 16; ++q) row(q);
             }
         }
         if (tid < GCH) {
@@ -792,7 +847,7 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
 #pragma unroll
         for (int h = 0; h < TPW; ++h)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) wph[h][j] = W1[(8 + j) * GW1 + s0 + 16 * h] * SPLIT_WSCALE;
+            for (int j = 0; j < 8; ++j) wph[h][j] = W1[(8 + j) * GW1 + s0 + 16 * h];
         // Software pipeline over the 2 CT (tap half, component tile) steps: the map
         // operands of step q + 1 are read from LDS before the products of step q.
         const half8 *ph = Ahi + lane, *pl = Alo + lane;  // step q = kh CT + ct at 64 q
@@ -806,18 +861,14 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
 #pragma unroll
             for (int h = 0; h < TPW; ++h) {
                 const float wt = W1[(4 * kh + grp) * GW1 + s0 + 16 * h];
-                float w8[8];
+                float x8[8];
+                // one rounding of the product, and both parts split from that value
+                // (fusing the product into either conversion would pair the two
+                // parts with differently rounded products)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    // one rounding of the product, and both parts split from that value
-                    // (fusing the product into either conversion would pair the two
-                    // parts with differently rounded products)
-                    const float x = as_is(wt * wph[h][j]);
-                    bh[h][j] = (_Float16)x;
-                    bl[h][j] = (_Float16)(x - (float)bh[h][j]);
-                    w8[j] = x * (1.f / SPLIT_RSCALE);
-                }
-                b8[h] = pack_fp8x8(w8);
+                for (int j = 0; j < 8; ++j) x8[j] = as_is(wt * wph[h][j]);
+                split_fp16x8(x8, bh[h], bl[h]);
+                b8[h] = pack_fp8x8_scaled(x8);
             }
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
@@ -939,15 +990,11 @@ __global__ void __launch_bounds__(256) k_gather_short(GatherDet D, int64_t cap) 
         long b8[2];
 #pragma unroll
         for (int kh = 0; kh < 2; ++kh) {
-            float w8[8];
+            float x8[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float x = as_is(wt[kh] * wph[j]);
-                bh[kh][j] = (_Float16)x;
-                bl[kh][j] = (_Float16)(x - (float)bh[kh][j]);
-                w8[j] = x * (1.f / SPLIT_RSCALE);
-            }
-            b8[kh] = pack_fp8x8(w8);
+            for (int j = 0; j < 8; ++j) x8[j] = as_is(wt[kh] * wph[j]);
+            split_fp16x8(x8, bh[kh], bl[kh]);
+            b8[kh] = pack_fp8x8_scaled(x8);
         }
         double sn, cs;
         sincos(ps, &sn, &cs);
@@ -972,15 +1019,12 @@ __global__ void __launch_bounds__(256) k_gather_short(GatherDet D, int64_t cap) 
 #pragma unroll
             for (int kh = 0; kh < 2; ++kh) {
                 half8 ah, al;
-                float rm[8];
+                float x8[8], rm[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float x = as_is(v[kh][j] * ms);  // exact (power of two)
-                    ah[j] = (_Float16)x;
-                    const float r1 = as_is(x - (float)ah[j]);  // exact
-                    al[j] = (_Float16)r1;
-                    rm[j] = (r1 - (float)al[j]) * SPLIT_RSCALE;  // exact; <= 2 significant bits
-                }
+                for (int j = 0; j < 8; ++j) x8[j] = as_is(v[kh][j] * ms);  // exact (power of two)
+                split_fp16x8(x8, ah, al, rm);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rm[j] *= SPLIT_RSCALE;  // exact; <= 2 significant bits
                 const long ar = pack_fp8x8(rm);
                 __builtin_amdgcn_sched_barrier(0);
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ar, b8[kh], acc, 0, 0, 0);

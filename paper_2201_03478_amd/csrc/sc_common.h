@@ -357,9 +357,9 @@ __device__ __forceinline__ void xcd_column_group(int b, int ncol, int ng, int &c
 __device__ __forceinline__ float es_weight_f32(float z, float nbl) {
     const float z2 = z * z;
     const float q = __builtin_fmaf(-z, z, 1.f);
-    if (!(q > 0.f)) return 0.f;
     const float s = __builtin_amdgcn_sqrtf(q);
-    return __builtin_amdgcn_exp2f(nbl * z2 * __builtin_amdgcn_rcpf(1.f + s));
+    const float w = __builtin_amdgcn_exp2f(nbl * z2 * __builtin_amdgcn_rcpf(1.f + s));
+    return q > 0.f ? w : 0.f;  // selected (the NaN of a negative q too), not branched over
 }
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
