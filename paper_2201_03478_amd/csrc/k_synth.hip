@@ -106,35 +106,8 @@ __device__ __forceinline__ void rec_step(const RecCoef &c, const double *x, doub
     }
 }
 
-// Steps t0 .. t1-1.  Four steps per iteration with two coefficient sets in
-// turn: the LDS reads of the next two steps are issued before the current two
-// steps' arithmetic (a scheduling barrier keeps them there), and an even step
-// count per iteration returns u / u_prev to the same registers, so neither the
-// loads nor the recursion need register moves.
-template <int RPT>
-__device__ __forceinline__ void rec_steps(int t0, int t1, const double *cA, const double *cBt, const double2 *cWp,
-                                          const double2 *cWm, const double *x, double *u, double *up, double2 *fp,
-                                          double2 *fm) {
-    const int te = t0 + ((t1 - t0) & ~3);
-    if (te > t0) {
-        RecCoef a0 = rec_load(t0, cA, cBt, cWp, cWm), a1 = rec_load(t0 + 1, cA, cBt, cWp, cWm);
-        for (int t = t0; t < te; t += 4) {
-            const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
-            __builtin_amdgcn_sched_barrier(0);
-            rec_step<RPT>(a0, x, u, up, fp, fm);
-            rec_step<RPT>(a1, x, u, up, fp, fm);
-            const int tn = t + 4 < te ? t + 4 : t;  // last iteration: harmless re-read
-            a0 = rec_load(tn, cA, cBt, cWp, cWm);
-            a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
-            __builtin_amdgcn_sched_barrier(0);
-            rec_step<RPT>(b0, x, u, up, fp, fm);
-            rec_step<RPT>(b1, x, u, up, fp, fm);
-        }
-    }
-    for (int t = te; t < t1; ++t) rec_step<RPT>(rec_load(t, cA, cBt, cWp, cWm), x, u, up, fp, fm);
-}
-
-// Up to 3 rings per lane the kernel fits 168 registers: three waves per SIMD.
+// One loop over the steps, fast or scaled: with separate loops the compiler kept the rings'
+// state in two sets of registers (166 at 3 rings per lane, 122 with one loop; spills past 5).
 template <int RPT, typename FT, bool TAB>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RPT <= 3 ? 3 : 2)))
 k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT *__restrict__ F,
@@ -207,18 +180,29 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
         if (TAB) cnext = chunk_coefs_tab(ccol, lc + 64, lane, l0, lmax);  // in flight during the steps
         const int nl = (lmax - lc + 1) < 64 ? (lmax - lc + 1) : 64;
         const double *cBt = cB + 64 * tp;
-        if (fast) {
-            rec_steps<RPT>(0, nl, cA, cBt, cWp, cWm, x, u, up, fp, fm);
-            continue;
-        }
+        // Four steps per iteration with two coefficient sets in turn: the LDS reads of the
+        // next two steps are issued before the current two steps' arithmetic (a scheduling
+        // barrier keeps them there), and an even step count per iteration returns u / u_prev
+        // to the same registers, so neither the loads nor the recursion need register moves.
+        // The last chunk is rounded up to whole iterations: steps past lmax have zero
+        // weights and coefficients.
         // Rescaling is checked once per 32 steps: one step grows |u| by at most
         // ~2^11, so 32 steps stay inside the 2^424 left below overflow, and what a
         // ring accumulates between passing 2^600 and its rescale (true values below
         // 2^{-600 + 352}) is dropped harmlessly with the scaled sums.
-        for (int t0 = 0; t0 < nl; t0 += 32) {
-            const int t1 = t0 + 32 < nl ? t0 + 32 : nl;
-            rec_steps<RPT>(t0, t1, cA, cBt, cWp, cWm, x, u, up, fp, fm);
-            if (fast) continue;
+        RecCoef a0 = rec_load(0, cA, cBt, cWp, cWm), a1 = rec_load(1, cA, cBt, cWp, cWm);
+        for (int t = 0; t < nl; t += 4) {
+            const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
+            __builtin_amdgcn_sched_barrier(0);
+            rec_step<RPT>(a0, x, u, up, fp, fm);
+            rec_step<RPT>(a1, x, u, up, fp, fm);
+            const int tn = (t + 4) & 63;  // last iteration: harmless re-read
+            a0 = rec_load(tn, cA, cBt, cWp, cWm);
+            a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
+            __builtin_amdgcn_sched_barrier(0);
+            rec_step<RPT>(b0, x, u, up, fp, fm);
+            rec_step<RPT>(b1, x, u, up, fp, fm);
+            if (fast || ((t & 28) != 28 && t + 4 < nl)) continue;
             bool low = false;
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
@@ -262,17 +246,21 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
 
 template <typename FT, bool TAB>
 static void launch_ring_sums(sc_plan *p, const double *alm, const double *blm, FT *F) {
-    const int nblk = (p->lmax + 1) * (p->kmax + 1) * p->ngroups;
+    const int nblk = (p->lmax + 1) * (p->kmax + 1) * p->ngroups_run;
     auto kern = k_ring_sums<4, FT, TAB>;
-    switch (p->rpt) {
+    switch (p->rpt_run) {
         case 1: kern = k_ring_sums<1, FT, TAB>; break;
         case 2: kern = k_ring_sums<2, FT, TAB>; break;
         case 3: kern = k_ring_sums<3, FT, TAB>; break;
+        case 5: kern = k_ring_sums<5, FT, TAB>; break;
+        case 7: kern = k_ring_sums<7, FT, TAB>; break;
+        case 8: kern = k_ring_sums<8, FT, TAB>; break;
+        case 9: kern = k_ring_sums<9, FT, TAB>; break;
         default: break;
     }
     hipLaunchKernelGGL(kern, dim3(nblk), dim3(64), 0, p->stream, (const double2 *)alm, (const double2 *)blm, F,
                        p->sbin_m, p->sbin_e, p->rtab, p->rroot, p->ctab, p->ctab_off, p->lmax, p->kmax, p->nring,
-                       p->ngroups, p->alm_lmax);
+                       p->ngroups_run, p->alm_lmax);
 }
 
 hipError_t sc_launch_ring_sums(sc_plan *p, const double *alm, const double *blm) {
@@ -353,4 +341,26 @@ void sc_choose_ring_layout(int nring, int *rpt, int *ngroups) {
     }
     *rpt = best_r;
     *ngroups = best_g;
+}
+
+// Layout the FP64 kernel runs with when none is set: up to nine rings per lane.  A longer
+// lane wastes fewer slots at some ring counts (lmax 384: 224 slots at 7 a lane, 256 at 4) and shares the coefficients of a chunk among more recursions; per slot, 4 and
+// more cost the same within a few percent.  lmax 384, kmax 45: 455 us at 4, 407 at 7; lmax
+// 2500, kmax 4: 9.23 ms at 4, 8.99 at 8; lmax 512, kmax 100: 1.92 ms at 3, 1.89 at 9 (6 is
+// nowhere better than 3).  It also leaves fewer waves, so more than 4 only where four waves
+// a SIMD remain: lmax 512 with 9 a lane, 5643 waves: 449 us a pass against 464 with 3, with
+// 3078 waves 299 against 280.
+void sc_choose_ring_layout_run(int nring, int ncol, int *rpt, int *ngroups) {
+    static const double cost[10] = {0.0, 1.65, 1.12, 1.0, 0.985, 0.97, 0.0, 0.985, 0.97, 0.97};
+    sc_choose_ring_layout(nring, rpt, ngroups);
+    double best = (double)*ngroups * *rpt * cost[*rpt];
+    for (int r = 5; r <= 9; ++r) {
+        const int g = sc_ring_groups(nring, r);
+        if (cost[r] == 0.0 || (int64_t)ncol * g < 4096) continue;
+        if ((double)g * r * cost[r] < best + 1e-9) {
+            best = (double)g * r * cost[r];
+            *rpt = r;
+            *ngroups = g;
+        }
+    }
 }
