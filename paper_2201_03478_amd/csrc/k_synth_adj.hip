@@ -299,18 +299,24 @@ k_ring_sums_adjoint(const double2 *__restrict__ FA, const double2 *__restrict__ 
     }
 }
 
-// grad[i] = sum over slabs and m of GB[slab][m][i], in that fixed order, over the blm
-// layout; the k = 0 column (entries i <= lmax) is real.
-__global__ void k_reduce_over_m(const double2 *__restrict__ GB, double2 *__restrict__ grad, int64_t nblm, int lmax,
-                                int nslab) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nblm) return;
+// grad[i] = sum over slabs and m of GB[slab][m][i], in a fixed order, over the blm layout;
+// the k = 0 column (entries i <= lmax) is real.  A workgroup takes 16 entries with 16 slices
+// of the sum each: one thread per entry left a serial chain of loads (lmax 128, kmax 8, 129
+// terms on five workgroups: 34 us).
+__global__ void __launch_bounds__(256) k_reduce_over_m(const double2 *__restrict__ GB, double2 *__restrict__ grad,
+                                                       int64_t nblm, int lmax, int nslab) {
+    __shared__ double2 part[256];
+    const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const int64_t i = (int64_t)blockIdx.x * 16 + e;
     double2 s = make_double2(0.0, 0.0);
-    for (int q = 0; q < nslab * (lmax + 1); ++q) {
-        const double2 v = GB[(size_t)q * nblm + i];
-        s.x += v.x;
-        s.y += v.y;
+    if (i < nblm) {
+#pragma unroll 4
+        for (int q = sl; q < nslab * (lmax + 1); q += 16) s = cadd(s, GB[(size_t)q * nblm + i]);
     }
+    part[threadIdx.x] = s;
+    __syncthreads();
+    if (sl > 0 || i >= nblm) return;
+    for (int q = 1; q < 16; ++q) s = cadd(s, part[16 * q + e]);
     if (i <= lmax) s.y = 0.0;
     grad[i] = s;
 }
@@ -377,7 +383,7 @@ hipError_t sc_launch_ring_sums_adjoint_beam(sc_plan *p, const double *alm, doubl
     hipError_t e = ring_sums_adjoint(p, alm, p->GB, true);
     if (e != hipSuccess) return e;
     const int64_t nblm = (int64_t)(p->kmax + 1) * (2 * p->lmax + 2 - p->kmax) / 2;
-    hipLaunchKernelGGL(k_reduce_over_m, dim3((unsigned)((nblm + 255) / 256)), dim3(256), 0, p->stream, p->GB,
+    hipLaunchKernelGGL(k_reduce_over_m, dim3((unsigned)((nblm + 15) / 16)), dim3(256), 0, p->stream, p->GB,
                        (double2 *)grad, nblm, p->lmax, sc_adjoint_slabs(p));
     return hipGetLastError();
 }
