@@ -542,16 +542,22 @@ hipError_t sc_launch_widen(const float2 *src, double2 *dst, size_t n, hipStream_
     return hipGetLastError();
 }
 
-// Size class of a transform of length n: 0 = (256 threads, 9 points each),
-// 1 = (512, 9), 2 = (1024, 9), 3 = (1024, 10): 9217 to 10240 points, complex128 in the
+// Size class of a transform of length n: 0 = (64 threads, 9 points each), 1 = (128, 9),
+// 2 = (256, 9), 3 = (512, 9), 4 = (1024, 9), 5 = (1024, 10).  The fewest threads that hold
+// the transform: a pass of radix R has n / R butterflies, so 256 threads at n = 540 left
+// three of four waves at the barriers (FP64 adjoint at lmax 128, kmax 8: theta 26 -> 19 us,
+// phi 25 -> 17 with 64; 100 and 280 band limits, FP32 maps: a few percent of the
+// convolution; no difference at n = 270).  Class 5: 9217 to 10240 points, complex128 in the
 // whole LDS of a CU.  One such workgroup per CU is still faster than the split stages,
 // whose columns are transformed singly and whose stores cross XCDs (lmax 2500, kmax 4:
 // theta 20 -> 2.7 ms, phi 7.2 -> 2.9 ms).
 static inline int fft_class(int n) {
-    return n <= SC_FFT_NT * SC_FFT_PT             ? 0
-           : n <= SC_FFT_NT_BIG * SC_FFT_PT       ? 1
-           : n <= SC_FFT_NT_HUGE * SC_FFT_PT_HUGE ? 2
-                                                  : 3;
+    return n <= 64 * SC_FFT_PT                    ? 0
+           : n <= 128 * SC_FFT_PT                 ? 1
+           : n <= SC_FFT_NT * SC_FFT_PT           ? 2
+           : n <= SC_FFT_NT_BIG * SC_FFT_PT       ? 3
+           : n <= SC_FFT_NT_HUGE * SC_FFT_PT_HUGE ? 4
+                                                  : 5;
 }
 
 template <int NT, int PT, typename S2, typename SOS, typename CT>
@@ -671,9 +677,11 @@ hipError_t sc_launch_theta_upsample(sc_plan *p) {
     if (p->n2 == 1080 && p->n2os == 2160) return theta_up<SC_FFT_NT, SC_FFT_PT, F1080, F2160>(p);
     if (p->n2 == 2160 && p->n2os == 4320) return theta_up<SC_FFT_NT_BIG, SC_FFT_PT, F2160, F4320>(p);
     switch (fft_class(p->n2os)) {
-        case 0: return theta_up<SC_FFT_NT, SC_FFT_PT>(p);
-        case 1: return theta_up<SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        case 2: return theta_up<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 0: return theta_up<64, SC_FFT_PT>(p);
+        case 1: return theta_up<128, SC_FFT_PT>(p);
+        case 2: return theta_up<SC_FFT_NT, SC_FFT_PT>(p);
+        case 3: return theta_up<SC_FFT_NT_BIG, SC_FFT_PT>(p);
+        case 4: return theta_up<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
         default: return theta_up_t<SC_FFT_NT_HUGE, SC_FFT_PT_FULL, FftGeneric, FftGeneric, double2>(p);
     }
 }
@@ -684,9 +692,11 @@ static hipError_t phi_syn_any(sc_plan *p) {
     if (p->nphi == 2160) return phi_syn<T, SC_FFT_NT, SC_FFT_PT, F2160>(p);
     if (p->nphi == 4320) return phi_syn<T, SC_FFT_NT_BIG, SC_FFT_PT, F4320>(p);
     switch (fft_class(p->nphi)) {
-        case 0: return phi_syn<T, SC_FFT_NT, SC_FFT_PT>(p);
-        case 1: return phi_syn<T, SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        case 2: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 0: return phi_syn<T, 64, SC_FFT_PT>(p);
+        case 1: return phi_syn<T, 128, SC_FFT_PT>(p);
+        case 2: return phi_syn<T, SC_FFT_NT, SC_FFT_PT>(p);
+        case 3: return phi_syn<T, SC_FFT_NT_BIG, SC_FFT_PT>(p);
+        case 4: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
         default: return phi_syn<T, SC_FFT_NT_HUGE, SC_FFT_PT_FULL, FftGeneric, false>(p);
     }
 }
@@ -702,9 +712,11 @@ static hipError_t phi_adj_any(sc_plan *p, const void *gmaps) {
     if (p->nphi == 2160) return phi_adj2<T, SC_FFT_NT, SC_FFT_PT, F2160>(p, gmaps);
     if (p->nphi == 4320) return phi_adj2<T, SC_FFT_NT_BIG, SC_FFT_PT, F4320>(p, gmaps);
     switch (fft_class(p->nphi)) {
-        case 0: return phi_adj<T, SC_FFT_NT, SC_FFT_PT>(p, gmaps);
-        case 1: return phi_adj<T, SC_FFT_NT_BIG, SC_FFT_PT>(p, gmaps);
-        case 2: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p, gmaps);
+        case 0: return phi_adj<T, 64, SC_FFT_PT>(p, gmaps);
+        case 1: return phi_adj<T, 128, SC_FFT_PT>(p, gmaps);
+        case 2: return phi_adj<T, SC_FFT_NT, SC_FFT_PT>(p, gmaps);
+        case 3: return phi_adj<T, SC_FFT_NT_BIG, SC_FFT_PT>(p, gmaps);
+        case 4: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p, gmaps);
         default: return phi_adj<T, SC_FFT_NT_HUGE, SC_FFT_PT_FULL>(p, gmaps);
     }
 }
@@ -730,9 +742,11 @@ hipError_t sc_launch_theta_adjoint(sc_plan *p) {
     if (p->n2 == 1080 && p->n2os == 2160) return theta_adj<SC_FFT_NT, SC_FFT_PT, F1080, F2160>(p);
     if (p->n2 == 2160 && p->n2os == 4320) return theta_adj<SC_FFT_NT_BIG, SC_FFT_PT, F2160, F4320>(p);
     switch (fft_class(p->n2os)) {
-        case 0: return theta_adj<SC_FFT_NT, SC_FFT_PT>(p);
-        case 1: return theta_adj<SC_FFT_NT_BIG, SC_FFT_PT>(p);
-        case 2: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
+        case 0: return theta_adj<64, SC_FFT_PT>(p);
+        case 1: return theta_adj<128, SC_FFT_PT>(p);
+        case 2: return theta_adj<SC_FFT_NT, SC_FFT_PT>(p);
+        case 3: return theta_adj<SC_FFT_NT_BIG, SC_FFT_PT>(p);
+        case 4: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_HUGE>(p);
         default: return theta_adj<SC_FFT_NT_HUGE, SC_FFT_PT_FULL>(p);
     }
 }
