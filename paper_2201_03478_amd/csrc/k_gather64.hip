@@ -11,15 +11,17 @@
 // result keeps the FP64 form's accuracy (1e-12 at W = 14).
 //
 // One wave per work item, no workgroup barriers.  The items hold at most 64 samples
-// (four 16-sample tiles, two when 32 or fewer are left; 16 or fewer take short64), and the
-// map values go from L2 straight into the A operand: one 8-byte load per lane (four columns
-// x 16 components) feeds a matrix instruction per sample tile.  Each tile holds the matrix
-// pipe for 64 cycles, so four tiles leave the caches 256 cycles per 512-byte operand (two tiles measured 1.15, one 2.0 ms where four take 0.91 ms).  The weights and phases
+// (four 16-sample tiles; one or two when 32 or fewer are left), and the map values go
+// from L2 straight into the A operand: one 8-byte load per lane (four columns x 16
+// components) feeds a matrix instruction per sample tile.  Each tile holds the matrix
+// pipe for 64 cycles, so four tiles leave the caches 256 cycles per 512-byte operand
+// (two tiles measured 1.15, one 2.0 ms where four take 0.91 ms).  The weights and phases
 // of the item's samples are in the wave's LDS.  Staging the block in LDS for 256-sample
 // passes instead held a CU to one workgroup (118 KB at W = 14), whose four waves waited
 // on each other, and computed 256 samples whatever the item held.  At W = 14: lmax 384,
 // kmax 45, 1e6 scan samples (about 125 per anchor) 1.55 -> 0.91 ms, 42 TFLOP/s of useful
-// products (63% of what a large FP64 matrix product reaches).
+// products (63% of what a large FP64 matrix product reaches); lmax 64, kmax 4, 1e5
+// uniform samples (3 per anchor) 3.17 -> 0.16 ms.
 //
 // Operand layout of the 16x16x4 FP64 instruction (checked on the device): A[i][k] in
 // lane i + 16 k, B[k][j] in lane j + 16 k, D[i][j] in lane j + 16 (i % 4), element
@@ -160,24 +162,15 @@ __device__ __forceinline__ void sweep(const char *__restrict__ blk, size_t rowb,
     }
 }
 
-// Pointers to global memory in a called function: generic ones would make flat loads there,
-// which count as LDS accesses too and so cannot stay in flight past an LDS read.
-#define SC_GLOBAL __attribute__((address_space(1)))
-
-// The workgroup's waves (one variable, so that a called function addresses it as LDS too).
-template <int W>
-__device__ __forceinline__ Wave64<W> *waves64() {
-    __shared__ Wave64<W> wsh[G64<W>::NWV];
-    return wsh;
-}
-
-// The tap weights and phases of samples pos0 .. pos0 + ns - 1 into the wave's LDS; returns the
-// index of sample `lane` (-1 past ns).
-template <int W, typename Rec>
-__device__ __forceinline__ int weights64(Rec rec, int pos0, int ns, Wave64<W> &sh, int lane,
-                                         double beta) {
+// The samples pos0 .. pos0 + ns - 1 (ns <= 16 T) of one anchor.
+template <int W, int T>
+__device__ __forceinline__ void samples64(const BinRec *__restrict__ rec, int pos0, int ns,
+                                          const char *__restrict__ blk, size_t rowb, const unsigned (&off)[G64<W>::NS],
+                                          int nct, int ncomp, unsigned dlast, Wave64<W> &sh, int lane, double beta,
+                                          double *__restrict__ tod) {
     using G = G64<W>;
     constexpr int HALF = W / 2;
+    const int r = lane & 15, grp = lane >> 4;
     // Weight of node e / 2^lp for sample e % 2^lp (theta nodes, then phi nodes), 2^lp >= ns.
     // Columns past ns are left as they are: they reach only the unused outputs of their own
     // sample slot.
@@ -202,142 +195,6 @@ __device__ __forceinline__ int weights64(Rec rec, int pos0, int ns, Wave64<W> &s
         sh.e1[lane] = e1;
         sh.e8[lane] = cmul(e4, e4);
     }
-    return idx;
-}
-
-// One sweep of short64 over the taps: component quads q0 .. q0 + N - 1 of 4 G samples, their
-// part of the k-sum added to part, z advanced to the next quad.
-template <int W, int G, int N>
-__device__ __forceinline__ void quads64(const SC_GLOBAL char *blk, unsigned rowb, int tileb, int col0, int q0,
-                                        int ncomp, const Wave64<W> &sh, int lane, double2 (&z)[G], double (&part)[G]) {
-    constexpr int WR = G64<W>::WR;
-    constexpr int NST = (W * W + 15) / 16;  // steps of 16 taps; taps past W^2 have weight zero
-    constexpr int D = NST < 4 ? NST : 4;    // steps in flight
-    const int i = lane & 3, di = lane >> 4;
-    const int t0 = ((lane >> 2) & 3) | (di << 2);  // the lane's tap of the first step
-    const unsigned compb = (i >> 1) * 128 + (i & 1) * 8;
-    // past ncomp (the last quad only) a lane reads the quad's first pair, left out below
-    const unsigned dlast = 4 * (q0 + N - 1) + i < ncomp ? 0u : 128u;
-    blk += q0 * 256;
-    double a[D][N];
-    int lr = t0 / W, lc = t0 - lr * W;  // tap of the next load
-    auto fetch = [&](int slot) {
-        const int c = col0 + lc;
-        const unsigned o = (unsigned)(lr < W ? lr : W - 1) * rowb + (c >> 3) * tileb + (c & 7) * 16 + compb;
-#pragma unroll
-        for (int q = 0; q < N; ++q) a[slot][q] = *(const SC_GLOBAL double *)(blk + 256 * q + (q == N - 1 ? o - dlast : o));
-        lr += 16 / W;
-        lc += 16 % W;
-        if (lc >= W) lc -= W, lr += 1;
-    };
-#pragma unroll
-    for (int s = 0; s < D; ++s) fetch(s);
-    double acc[N][G];
-#pragma unroll
-    for (int q = 0; q < N; ++q)
-#pragma unroll
-        for (int g = 0; g < G; ++g) acc[q][g] = 0.0;
-    int ur = t0 / W, uc = t0 - ur * W;  // tap of the next product
-#pragma unroll 1
-    for (int s0 = 0; s0 < NST; s0 += D)
-#pragma unroll
-        for (int s = 0; s < D; ++s) {
-            if (NST % D && s0 + s >= NST) break;
-            const double *wt = sh.w + (ur < W ? ur : W - 1) * WR + i, *wp = sh.w + (W + uc) * WR + i;
-            double b[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const double w = wt[4 * g] * wp[4 * g];
-                b[g] = W * W % 16 && ur >= W ? 0.0 : w;
-            }
-#pragma unroll
-            for (int q = 0; q < N; ++q)
-#pragma unroll
-                for (int g = 0; g < G; ++g)
-                    acc[q][g] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[s][q], b[g], acc[q][g], 0, 0, 0);
-            ur += 16 / W;
-            uc += 16 % W;
-            if (uc >= W) uc -= W, ur += 1;
-            if (s0 + s + D < NST) fetch(s);
-        }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const double2 e1 = sh.e1[4 * g + i], e2 = cmul(e1, e1);
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-            const double x = q < N - 1 || 4 * (q0 + q) + di < ncomp ? acc[q][g] : 0.0;
-            part[g] = fma(di & 1 ? z[g].y : z[g].x, x, part[g]);
-            z[g] = cmul(z[g], e2);
-        }
-    }
-}
-
-// Up to 4 G <= 16 samples of one anchor.  A 16x16x4 product would compute 16 samples
-// whatever the item holds, and its operand load takes one column of 16 components per
-// quarter of the wave, that is 32 half lines per load, which is what such items then wait
-// for.  v_mfma_f64_4x4x4_4b has four independent 4x4x4 products (92% of the 16x16x4 rate
-// when measured alone); the four blocks here take four columns of the same four components
-// each, so a load covers 4 components x 16 consecutive taps in 8 half lines and a quarter of
-// the products serve four samples.  Layout (checked on the device): A[i][k] of block b in
-// lane i + 4 b + 16 k, B[k][j] in lane j + 4 b + 16 k, D[i][j] in lane j + 4 b + 16 i; tap
-// 16 step + 4 k + b, component 4 q + i.  The blocks' sums are added with the k-sum.
-// lmax 64, kmax 4, W = 14, 1e5 uniform samples (3 per anchor): 159 -> 116 us; lmax
-// 512, kmax 45, 1e6 uniform samples (mostly alone in their item): convolution 29.0 -> 15.3 ms.
-// As a kernel of its own with four waves a SIMD it takes 83 us there, but the few short items
-// of a scan then wait for a launch after the long ones (lmax 130, kmax 20, 3e4 samples: 144
-// -> 159 us).  A called function, because its registers would make the long items spill.
-template <int W, int G>
-__device__ __noinline__ void short64(const SC_GLOBAL BinRec *rec, int pos0, int ns, const SC_GLOBAL char *blk,
-                                     unsigned rowb, int tileb, int col0, int ncomp, int lane, double beta,
-                                     SC_GLOBAL double *tod) {
-    Wave64<W> &sh = waves64<W>()[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
-    // arguments of a call come in vector registers: back to scalars, all are wave-uniform
-    pos0 = __builtin_amdgcn_readfirstlane(pos0), ns = __builtin_amdgcn_readfirstlane(ns);
-    rowb = __builtin_amdgcn_readfirstlane(rowb), tileb = __builtin_amdgcn_readfirstlane(tileb);
-    col0 = __builtin_amdgcn_readfirstlane(col0), ncomp = __builtin_amdgcn_readfirstlane(ncomp);
-    const uint64_t at = (uint64_t)blk;
-    blk = (const SC_GLOBAL char *)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32 |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)at));
-    const int i = lane & 3, di = lane >> 4;
-    const int idx = weights64<W>(rec, pos0, ns, sh, lane, beta);
-    wave_lds_sync();
-    double2 z[G];
-    double part[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        z[g] = di < 2 ? make_double2(1.0, 0.0) : sh.e1[4 * g + i];  // e^{i k psi}, k = 2 q + di / 2
-        part[g] = 0.0;
-    }
-    // component quads four at a time, then the rest
-    const int nq = (ncomp + 3) >> 2;
-    int q0 = 0;
-#pragma unroll 1
-    for (; q0 + 4 <= nq; q0 += 4) quads64<W, G, 4>(blk, rowb, tileb, col0, q0, ncomp, sh, lane, z, part);
-    if (nq - q0 == 3)
-        quads64<W, G, 3>(blk, rowb, tileb, col0, q0, ncomp, sh, lane, z, part);
-    else if (nq - q0 == 2)
-        quads64<W, G, 2>(blk, rowb, tileb, col0, q0, ncomp, sh, lane, z, part);
-    else if (nq - q0 == 1)
-        quads64<W, G, 1>(blk, rowb, tileb, col0, q0, ncomp, sh, lane, z, part);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int off = 4; off < 64; off <<= 1) part[g] += __shfl_xor(part[g], off);
-        const int ix = __shfl(idx, 4 * g + i);
-        if (lane < 4 && ix >= 0) tod[ix] = part[g];
-    }
-    wave_lds_sync();  // the weights and phases are rewritten by the next samples
-}
-
-// The samples pos0 .. pos0 + ns - 1 (ns <= 16 T) of one anchor.
-template <int W, int T>
-__device__ __forceinline__ void samples64(const BinRec *__restrict__ rec, int pos0, int ns,
-                                          const char *__restrict__ blk, size_t rowb, const unsigned (&off)[G64<W>::NS],
-                                          int nct, int ncomp, unsigned dlast, Wave64<W> &sh, int lane, double beta,
-                                          double *__restrict__ tod) {
-    using G = G64<W>;
-    const int r = lane & 15, grp = lane >> 4;
-    const int idx = weights64<W>(rec, pos0, ns, sh, lane, beta);
     wave_lds_sync();
     double2 q[T];
 #pragma unroll
@@ -374,7 +231,7 @@ k_gather_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals, 
                 const double *__restrict__ maps, double *__restrict__ tod, int cols, int ncp, int ncomp, int nkc,
                 double beta) {
     using G = G64<W>;
-    Wave64<W> *wsh = waves64<W>();
+    __shared__ Wave64<W> wsh[G::NWV];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, grp = lane >> 4;
@@ -402,9 +259,6 @@ k_gather_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals, 
             const int c = col0 + j;
             off[s] = (c >> 3) * tileb + (c & 7) * 16 + compb + (t < W ? 0u : (unsigned)rowb);
         }
-        const SC_GLOBAL BinRec *grec = (const SC_GLOBAL BinRec *)srt.rec;
-        const SC_GLOBAL char *gblk = (const SC_GLOBAL char *)blk;
-        SC_GLOBAL double *gtod = (SC_GLOBAL double *)tod;
         for (int ch = 0; ch < item.z; ch += 16 * G::TS) {
             const int left = item.z - ch;
             if (left > 32)
@@ -412,12 +266,8 @@ k_gather_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals, 
                                 lane, beta, tod);
             else if (left > 16)
                 samples64<W, 2>(srt.rec, item.y + ch, left, blk, rowb, off, nct, ncomp, dlast, wsh[wv], lane, beta, tod);
-            else if (left > 8)
-                short64<W, 4>(grec, item.y + ch, left, gblk, (unsigned)rowb, tileb, col0, ncomp, lane, beta, gtod);
-            else if (left > 4)
-                short64<W, 2>(grec, item.y + ch, left, gblk, (unsigned)rowb, tileb, col0, ncomp, lane, beta, gtod);
             else
-                short64<W, 1>(grec, item.y + ch, left, gblk, (unsigned)rowb, tileb, col0, ncomp, lane, beta, gtod);
+                samples64<W, 1>(srt.rec, item.y + ch, left, blk, rowb, off, nct, ncomp, dlast, wsh[wv], lane, beta, tod);
         }
     }
 }
