@@ -306,8 +306,7 @@ hipError_t sc_launch_rec_table(sc_plan *p) {
     return hipGetLastError();
 }
 
-// Rings per lane: the fewest wasted lane slots with at most 4 rings per lane
-// (more rings per lane spill registers).  A wave covers 32 RPT northern rings with
+// Rings per lane: the fewest wasted lane slots with at most 4 rings per lane.  A wave covers 32 RPT northern rings with
 // each of the two recursions.
 int sc_ring_groups(int nring, int rpt) {
     const int nh = (nring + 1) / 2;
@@ -344,12 +343,13 @@ void sc_choose_ring_layout(int nring, int *rpt, int *ngroups) {
 }
 
 // Layout the FP64 kernel runs with when none is set: up to nine rings per lane.  A longer
-// lane wastes fewer slots at some ring counts (lmax 384: 224 slots at 7 a lane, 256 at 4) and shares the coefficients of a chunk among more recursions; per slot, 4 and
-// more cost the same within a few percent.  lmax 384, kmax 45: 455 us at 4, 407 at 7; lmax
-// 2500, kmax 4: 9.23 ms at 4, 8.99 at 8; lmax 512, kmax 100: 1.92 ms at 3, 1.89 at 9 (6 is
-// nowhere better than 3).  It also leaves fewer waves, so more than 4 only where four waves
-// a SIMD remain: lmax 512 with 9 a lane, 5643 waves: 449 us a pass against 464 with 3, with
-// 3078 waves 299 against 280.
+// lane wastes fewer slots at some ring counts (lmax 384: 224 slots at 7 a lane, 256 at 4) and
+// shares the coefficients of a chunk among more recursions; per slot, 4 and more cost the
+// same within a few percent.  lmax 384, kmax 45: 455 us at 4, 407 at 7; lmax 2500, kmax 4:
+// 9.23 ms at 4, 8.99 at 8; lmax 512, kmax 100: 1.92 ms at 3, 1.89 at 9 (6 is nowhere better
+// than 3).  It also leaves fewer waves, so more than 4 only where four waves a SIMD remain:
+// lmax 512 with 9 a lane, 5643 waves: 449 us a pass against 464 with 3, with 3078 waves 299
+// against 280.
 void sc_choose_ring_layout_run(int nring, int ncol, int *rpt, int *ngroups) {
     static const double cost[10] = {0.0, 1.65, 1.12, 1.0, 0.985, 0.97, 0.0, 0.985, 0.97, 0.97};
     sc_choose_ring_layout(nring, rpt, ngroups);
