@@ -237,6 +237,13 @@ int sc_convolve_release_cache(void);
  * workgroups of at most 2048 rings; longer columns (lmax >= 2048) are split
  * into ring slabs whose partial gradients are added in a fixed order, so the
  * gradient workspace grows by the slab count (ceil(rings / 2048)).
+ * Workspace beyond the plan's: the gradient maps and per-k gradients (first call),
+ * and for binning the samples 56 bytes per sample.  FP32 plans share the
+ * interpolation's (passes of at most 2^27 samples).  FP64 plans hold their own, 12
+ * bytes per interpolation anchor and room for passes of at most 2^24 samples, which
+ * grows to the largest n seen (the buffers it outgrows are kept until the plan is
+ * destroyed: twice that at most); where it cannot be allocated, or would have to grow
+ * while the stream is being captured, they scatter sample by sample without it.
  */
 int sc_convolve_adjoint(sc_plan *plan, const double *blm, const double *ptg, const void *tod_grad, int64_t n,
                         double *alm_grad);

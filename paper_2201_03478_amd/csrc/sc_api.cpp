@@ -200,10 +200,77 @@ int ensure_bin_work(sc_plan *p, int64_t need) {
     return SC_OK;
 }
 
+// Whether work queued on `s` now is recorded into a graph (or cannot be queried while one is).
+bool stream_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The FP64 adjoint's own binning workspace, for passes of up to `need` samples; false if it
+// cannot be had (the adjoint then scatters sample by sample, which needs none).  The plan's
+// graphs may hold its addresses, so it is apart from the interpolation's, never grows while
+// the stream is captured, and the sample buffers that a larger set replaces are kept until
+// the plan is destroyed: each set is at least twice the one before, so together they hold
+// no more than the current one.  The per-anchor tables do not depend on the sample count.
+bool ensure_adj_bin_work(sc_plan *p, int64_t need) {
+    BinWork &w = p->abw;
+    if (w.cap >= need) return true;
+    if (p->nabw_old == SC_ABW_SETS || stream_capturing(p->stream)) return false;
+    hipStream_t s = p->stream;
+    BinWork n = w;
+    size_t tot = 0;
+    int rc = SC_OK;
+    if (!n.count) {
+        const BinGeom g = sc_bin_geom(p);
+        n.nkeys = (int64_t)g.nkr * g.nkc;
+        rc = rc ? rc : alloc_async((void **)&n.count, sizeof(int) * n.nkeys, &tot, s);
+        rc = rc ? rc : alloc_async((void **)&n.offs, sizeof(int2) * n.nkeys, &tot, s);
+        rc = rc ? rc : alloc_async((void **)&n.sums, sizeof(int2) * ((n.nkeys + 4095) / 4096), &tot, s);
+        rc = rc ? rc : alloc_async((void **)&n.totals, sizeof(int) * 4, &tot, s);
+    }
+    n.cap = std::max(need, std::max<int64_t>(2 * w.cap, BIN_SMALL));
+    n.key = n.rank = nullptr;
+    n.sorted.rec = nullptr;
+    n.items = nullptr;
+    rc = rc ? rc : alloc_async((void **)&n.key, sizeof(int) * n.cap, &tot, s);
+    rc = rc ? rc : alloc_async((void **)&n.rank, sizeof(int) * n.cap, &tot, s);
+    rc = rc ? rc : alloc_async((void **)&n.sorted.rec, sizeof(BinRec) * n.cap, &tot, s);
+    rc = rc ? rc : alloc_async((void **)&n.items, sizeof(int4) * n.cap, &tot, s);
+    if (rc) {
+        if (w.count) n.count = nullptr, n.offs = nullptr, n.sums = nullptr, n.totals = nullptr;  // still w's
+        free_bin_work(n, s);
+        g_msg[0] = 0;
+        return false;
+    }
+    if (w.key) p->abw_old[p->nabw_old++] = w;
+    w = n;
+    w.bytes += tot;
+    p->ws_bytes += tot;
+    return true;
+}
+
+// The launchers take their binning buffers from p->bw: the adjoint's stand there for its passes.
+struct AdjBinScope {
+    sc_plan *p;
+    BinWork own;
+    explicit AdjBinScope(sc_plan *plan) : p(plan), own(plan->bw) { p->bw = p->abw; }
+    ~AdjBinScope() { p->bw = own; }
+};
+
 // Release every buffer of a plan (the caller has synchronised its stream; the
 // stream-ordered ones are returned on the stream, which the caller then waits for).
 void free_plan_buffers(sc_plan *p) {
     free_bin_work(p->bw, p->stream);
+    for (int i = 0; i < p->nabw_old; ++i) {
+        void *set[] = {p->abw_old[i].key, p->abw_old[i].rank, p->abw_old[i].sorted.rec, p->abw_old[i].items};
+        for (void *b : set) (void)hipFreeAsync(b, p->stream);
+    }
+    p->nabw_old = 0;
+    free_bin_work(p->abw, p->stream);
     {
         void *pool[] = {p->twpsi, p->gpsi, p->cube};
         for (void *b : pool)
@@ -932,9 +999,10 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
         } else {
             // FP64: binned on the matrix cores; sample by sample if the binning workspace cannot
             // be had (or the plan takes the per-sample path)
-            const int64_t pass = n < p->bin_pass_max ? n : p->bin_pass_max;
-            const bool binned = sc_scatter64_supported(p) && ensure_bin_work(p, pass) == SC_OK;
+            const int64_t pass = std::min<int64_t>(n, std::min<int64_t>(p->bin_pass_max, BIN_PASS_ADJ64));
+            const bool binned = sc_scatter64_supported(p) && ensure_adj_bin_work(p, pass);
             if (binned) {
+                const AdjBinScope scope(p);
                 for (int64_t off = 0; off < n; off += pass) {
                     const int64_t cnt = n - off < pass ? n - off : pass;
                     slot = timing_begin(p, SC_STAGE_BIN);
@@ -947,7 +1015,6 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
                     if (e != hipSuccess) return hip_fail(e, "scatter launch");
                 }
             } else {
-                g_msg[0] = 0;
                 slot = timing_begin(p, SC_STAGE_SCATTER);
                 e = sc_launch_scatter(p, ptg, n, tod_grad, p->gmaps);
                 timing_end(p, slot);

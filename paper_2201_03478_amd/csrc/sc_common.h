@@ -48,6 +48,10 @@ struct FftPlan {
 // ... of the FP64 scatter, whose workgroup keeps one item's weights in LDS.
 #define BIN_CHUNK_SC64 128
 #define BIN_PASS_MAX (1 << 27)
+// Samples per binning pass of the FP64 adjoint, whose workspace is its own (0.94 GB at most).
+#define BIN_PASS_ADJ64 (1 << 24)
+// Sets of sample buffers that workspace may have gone through (each at least twice the last).
+#define SC_ABW_SETS 16
 
 // Passes of at most this many samples are binned by one workgroup (one launch).
 #define BIN_SMALL 4096
@@ -163,6 +167,9 @@ struct sc_plan {
     int have_maps;
     size_t ws_bytes;
     BinWork bw;        // stream-ordered allocations (hipMallocAsync / hipFreeAsync on the plan's stream)
+    BinWork abw;       // FP64 adjoint: its own binning workspace, allocated like bw
+    BinWork abw_old[SC_ABW_SETS];  // ... and the sample buffers it outgrew, kept for graphs that hold them
+    int nabw_old;
     void *gmaps;       // adjoint: gradient maps, [rows][cols][ncp] in both precisions (allocated on first use)
     double2 *GA;       // adjoint: per-k gradient contributions [kmax+1][n_alm]
     double2 *GB;       // beam adjoint: per-m gradient contributions [lmax+1][n_blm] (allocated on first use)
