@@ -3,7 +3,8 @@
     python -m paper_2201_03478_amd.build
 
 Every source is compiled for gfx950 only, with packed FP32 instructions
-disabled, and linked into paper_2201_03478_amd/libsidelobe.so.
+disabled, checked for the order of its matrix products (product_order.py), and
+linked into paper_2201_03478_amd/libsidelobe.so.
 """
 from __future__ import annotations
 
@@ -12,6 +13,8 @@ import os
 import shutil
 import subprocess
 import sys
+
+from . import product_order
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -34,6 +37,8 @@ def _compile(src: str) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, " ".join(cmd), r.stderr))
+    if src.endswith(".hip"):
+        product_order.check(obj)
     return obj
 
 

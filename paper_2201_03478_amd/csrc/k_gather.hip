@@ -598,7 +598,7 @@ struct SlideLds {
 template <int CT, int NWV, bool SLIDE = false>
 __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4 item, double *smem_d, unsigned *smax,
                                                   SlideLds *sl = nullptr, bool reuse = false) {
-    static_assert(NWV == 4 && GCH == 128, "the weight rows below are shared out for two pairs of waves");
+    static_assert(NWV == 4 && GCH == 128, "two sample tiles a wave (their products take turns), weight rows for two pairs of waves");
     constexpr int NT = 64 * NWV;
     constexpr int TPW = 8 / NWV;
     constexpr int NC = 16 * CT;
@@ -877,7 +877,11 @@ __device__ __forceinline__ void gather_split_item(const GatherDet &D, const int4
                 const half8 ahn = ph[64 * qn], aln = pl[64 * qn];
                 const long arn = pr[64 * qn];
                 __builtin_amdgcn_sched_barrier(0);
-                // smallest terms first
+                // Smallest terms first.  The tiles take turns, so that no product stands right
+                // behind one of the other format on its accumulator: the results would be others
+                // (product_order.py, with which the build checks it: barriers between the products
+                // or another wording of these loops have let the compiler move some together, and
+                // waits in every step cost 3 to 13% of the interpolation).
 #pragma unroll
                 for (int h = 0; h < TPW; ++h)
                     acc[h][ct] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ar, b8[h], acc[h][ct], 0, 0, 0);
@@ -1028,9 +1032,8 @@ __global__ void __launch_bounds__(256) k_gather_short(GatherDet D, int64_t cap) 
                 const long ar = pack_fp8x8(rm);
                 __builtin_amdgcn_sched_barrier(0);
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(ar, b8[kh], acc, 0, 0, 0);
-                // An FP16 product right behind the FP8 product that wrote its accumulator reads
-                // it too early (and the other way round): wait in between.  In gather_split_item
-                // the other sample tile's product stands there.
+                // An FP16 product right behind the FP8 product on its accumulator (and the other
+                // way round) gives other bits, and the compiler keeps no distance: wait in between.
                 asm volatile("s_nop 15" : "+v"(acc));
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bl[kh], acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh[kh], acc, 0, 0, 0);
