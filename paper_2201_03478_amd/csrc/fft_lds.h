@@ -223,17 +223,23 @@ __device__ __forceinline__ void dft_small(double2 *v) {
 // One Stockham pass of radix R.
 
 // A pass is bound by latency (two thirds of the waves' time at 10240 points, one workgroup a
-// CU), so a butterfly's twiddles w^r, r < R, are formed from its base w: only that is
-// loaded, before the pass's LDS reads, and the base rows of a transform fit the L1.  Loading
-// all R - 1 of them from L2: lmax 2500, kmax 4: theta 3.11, phi 3.01 ms, now 2.32 and 2.10;
-// FP64 lmax 384, kmax 45: 467 and 487 us, now 391 and 440.
-template <int R, int DIR, int NT, int PT>
+// CU), so of a butterfly's twiddles w^r, r < R, only w, w^2, w^4 and w^8 are loaded, before
+// the pass's LDS reads; the others are products of two or three of them, which leaves the
+// transform's error where loading all has it (within 5%; with powers of w alone up to 1.9
+// times, seen in the results at W = 16).  Loading all from L2 against this: lmax 2500, kmax 4:
+// theta 3.11 -> 1.95 ms, phi 3.01 -> 2.25; lmax 700, kmax 30: 915 -> 745 us, 1061 -> 865.
+// ALL loads every twiddle: for the split theta stages, which are slower with fewer loads (they
+// run at the limit of the registers and at the pace of their column-strided accesses; lmax
+// 2600, kmax 1: 7.9 ms against 13.0, adjoint transforms 13.5 against 17.7).  The split phi
+// stages gain (2.37 -> 1.99 ms).
+template <int R, int DIR, int NT, int PT, bool ALL>
 __device__ __forceinline__ void stockham_stage(double2 *buf, int N, int Ns, unsigned mag,
                                                const double2 *__restrict__ tw, int tid, int nth) {
     constexpr int B = (PT + R - 1) / R;  // butterflies per thread: B NT >= N / R since N <= NT PT
+    constexpr int NP = R > 8 ? 4 : R > 4 ? 3 : R > 2 ? 2 : 1;  // powers of two below R
     const int nb = N / R;
-    double2 v[B][R], w1[B];
-    int widx[B];
+    double2 v[B][R], wp[B][NP];
+    int widx[B], kb[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         const int j = tid + b * nth;
@@ -241,30 +247,38 @@ __device__ __forceinline__ void stockham_stage(double2 *buf, int N, int Ns, unsi
         const int g = Ns > 1 ? (int)__umulhi((unsigned)j, mag) : j;
         const int k = j - g * Ns;
         widx[b] = g * Ns * R + k;
-        w1[b] = make_double2(1.0, 0.0);
-        if (Ns > 1 && j < nb) w1[b] = tw[(Ns - 1) + k];  // pass-major table: its first row
+        kb[b] = k;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            wp[b][q] = make_double2(1.0, 0.0);
+            if (!ALL && Ns > 1 && j < nb) wp[b][q] = tw[((1 << q) * Ns - 1) + k];  // pass-major: w^r at (r - 1) Ns
+            if (DIR > 0) wp[b][q].y = -wp[b][q].y;
+        }
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         const int j = tid + b * nth;
         if (j < nb) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[b][r] = buf[j + r * nb];
-            if (Ns > 1) {
-                double2 w = w1[b];
-                if (DIR > 0) w.y = -w.y;
-                // two chains of products: w, w^3, ... and w^2, w^4, ...
-                const double2 w2 = cmul(w, w);
-                double2 wo = w, we = w2;
+            for (int r = 0; r < R; ++r) {
+                v[b][r] = buf[j + r * nb];
+                if (ALL && r > 0 && Ns > 1) {
+                    double2 w = tw[r * Ns - 1 + kb[b]];
+                    if (DIR > 0) w.y = -w.y;
+                    v[b][r] = cmul(v[b][r], w);
+                }
+            }
+            if (!ALL && Ns > 1) {
+                // w^r = w^{r mod 4} w^{4 (r / 4)}
+                const double2 w1 = wp[b][0], w2 = NP > 1 ? wp[b][1] : w1, w3 = cmul(w1, w2);
+                double2 hi = w1;
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-                    if (r & 1) {
-                        v[b][r] = cmul(v[b][r], wo);
-                        if (r + 2 < R) wo = cmul(wo, w2);
-                    } else {
-                        v[b][r] = cmul(v[b][r], we);
-                        if (r + 2 < R) we = cmul(we, w2);
-                    }
+                    if (r == 4) hi = wp[b][NP > 2 ? 2 : 0];
+                    if (r == 8) hi = wp[b][NP > 3 ? 3 : 0];
+                    if (r == 12) hi = cmul(wp[b][NP > 2 ? 2 : 0], hi);
+                    const double2 lo = (r & 3) == 1 ? w1 : (r & 3) == 2 ? w2 : w3;
+                    v[b][r] = cmul(v[b][r], r < 4 ? lo : (r & 3) == 0 ? hi : cmul(hi, lo));
                 }
             }
             dft_small<R, DIR>(v[b]);
@@ -284,23 +298,23 @@ __device__ __forceinline__ void stockham_stage(double2 *buf, int N, int Ns, unsi
 
 // In-place transform of buf[0 .. P.n) (LDS) by NT threads; requires P.n <= NT PT.
 // Starts and ends with a barrier-complete buffer.
-template <int DIR, int NT, int PT>
+template <int DIR, int NT, int PT, bool ALL = false>
 __device__ void fft_lds(double2 *buf, const FftPlan &P, const double2 *__restrict__ tw, int tid, int nth) {
     for (int s = 0; s < P.nst; ++s) {
         const int R = P.r[s], Ns = P.ns[s];
         const unsigned mg = P.mag[s];
         switch (R) {
-            case 2: stockham_stage<2, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 3: stockham_stage<3, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 4: stockham_stage<4, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 5: stockham_stage<5, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 6: stockham_stage<6, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 8: stockham_stage<8, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 9: stockham_stage<9, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 10: stockham_stage<10, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 12: stockham_stage<12, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            case 15: stockham_stage<15, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
-            default: stockham_stage<16, DIR, NT, PT>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 2: stockham_stage<2, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 3: stockham_stage<3, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 4: stockham_stage<4, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 5: stockham_stage<5, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 6: stockham_stage<6, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 8: stockham_stage<8, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 9: stockham_stage<9, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 10: stockham_stage<10, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 12: stockham_stage<12, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            case 15: stockham_stage<15, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
+            default: stockham_stage<16, DIR, NT, PT, ALL>(buf, P.n, Ns, mg, tw, tid, nth); break;
         }
     }
 }

@@ -37,7 +37,7 @@ __device__ __forceinline__ double2 cis_frac(int a, int n, int dir) {
 
 // Pass s of a split transform of length n = P Q.n: buf <- y_s (input x(t), t < n, from
 // `in`), then the LDS transform; on return buf[k] = X[P k + s].  Ends barrier-complete.
-template <int DIR, typename In>
+template <int DIR, bool ALL, typename In>
 __device__ void split_pass(double2 *buf, const FftPlan &Q, const double2 *__restrict__ tw, int P, int s, int n,
                            In in, int tid) {
     const int N = Q.n;
@@ -53,7 +53,7 @@ __device__ void split_pass(double2 *buf, const FftPlan &Q, const double2 *__rest
         buf[j] = acc;
     }
     __syncthreads();
-    fft_lds<DIR, BNT, BPT>(buf, Q, tw, tid, BNT);
+    fft_lds<DIR, BNT, BPT, ALL>(buf, Q, tw, tid, BNT);
 }
 
 // Global writes of this workgroup visible to its later global reads.
@@ -86,7 +86,7 @@ k_theta_upsample_big(const double2 *__restrict__ F, double2 *__restrict__ G, dou
         return make_double2(s1 * v.x, s1 * v.y);
     };
     for (int s = 0; s < P1; ++s) {
-        split_pass<-1>(sbuf, Q1, tw1, P1, s, n2, xin, tid);
+        split_pass<-1, true>(sbuf, Q1, tw1, P1, s, n2, xin, tid);
         for (int kk = tid; kk < Q1.n; kk += BNT) {
             const int n = P1 * kk + s;
             const int ns = n <= n2 / 2 ? n : n - n2;
@@ -107,7 +107,7 @@ k_theta_upsample_big(const double2 *__restrict__ F, double2 *__restrict__ G, dou
     const int r0 = -W / 2 + 1, rtop = r0 + rows - 1;
     double2 *gcol = G + (size_t)k * rows * nm + mi;
     for (int s = 0; s < P2; ++s) {
-        split_pass<1>(sbuf, Q2, tw2, P2, s, nos, zin, tid);
+        split_pass<1, true>(sbuf, Q2, tw2, P2, s, nos, zin, tid);
         for (int rr = tid; rr < Q2.n; rr += BNT) {
             const int r = P2 * rr + s;
             const int row = r <= rtop ? r - r0 : (r - nos >= r0 ? r - nos - r0 : -1);
@@ -150,7 +150,7 @@ k_phi_synthesis_big(const double2 *__restrict__ G, T *__restrict__ maps, int lma
     };
     const int q0 = -W / 2 + 1;
     for (int s = 0; s < P; ++s) {
-        split_pass<1>(sbuf, Q, tw, P, s, nphi, gin, tid);
+        split_pass<1, false>(sbuf, Q, tw, P, s, nphi, gin, tid);
         for (int qq = tid; qq < Q.n; qq += BNT) {
             const int q = P * qq + s;
             const double2 v = comp_pair(sbuf[qq], k);
@@ -190,7 +190,7 @@ k_phi_adjoint_big(const T *__restrict__ gmaps, double2 *__restrict__ G, int lmax
     };
     double2 *dst = G + ((size_t)k * rows + row) * nm;
     for (int s = 0; s < P; ++s) {
-        split_pass<-1>(sbuf, Q, tw, P, s, nphi, uin, tid);
+        split_pass<-1, false>(sbuf, Q, tw, P, s, nphi, uin, tid);
         for (int kk = tid; kk < Q.n; kk += BNT) {
             const int n = P * kk + s;
             const int ms = n <= nphi / 2 ? n : n - nphi;
@@ -223,7 +223,7 @@ k_theta_adjoint_big(double2 *__restrict__ G, double2 *__restrict__ S, int lmax, 
         return row >= 0 ? gcol[(size_t)row * nm] : zero;
     };
     for (int s = 0; s < P2; ++s) {
-        split_pass<-1>(sbuf, Q2, tw2, P2, s, nos, ain, tid);
+        split_pass<-1, true>(sbuf, Q2, tw2, P2, s, nos, ain, tid);
         for (int kk = tid; kk < Q2.n; kk += BNT) {
             const int n = P2 * kk + s;
             const int ns = n <= nos / 2 ? n : n - nos;
@@ -241,7 +241,7 @@ k_theta_adjoint_big(double2 *__restrict__ G, double2 *__restrict__ S, int lmax, 
         return zero;
     };
     for (int s = 0; s < P1; ++s) {
-        split_pass<1>(sbuf, Q1, tw1, P1, s, n2, zin, tid);
+        split_pass<1, true>(sbuf, Q1, tw1, P1, s, n2, zin, tid);
         for (int jj = tid; jj < Q1.n; jj += BNT) gcol[(size_t)(P1 * jj + s) * nm] = sbuf[jj];
         __syncthreads();
     }
