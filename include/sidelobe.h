@@ -319,7 +319,9 @@ int sc_plan_stage_times(sc_plan *plan, double *ms, int64_t *launches, int nstage
  * package; defaults work everywhere).
  *   SC_PARAM_BIN_CHUNK          samples per gather/scatter work item, 16 .. 2^20 (default 256)
  *   SC_PARAM_GATHER_WGS_PER_CU  persistent gather/scatter workgroups per CU, 0 = as many as fit
- *   SC_PARAM_RING_RPT           northern rings per lane and recursion of the ring-sum kernel, 1..4
+ *   SC_PARAM_RING_RPT           northern rings per lane and recursion of the ring-sum kernel in use:
+ *                               1 to 5 and 7 to 9 (SC_MIXED: 1 to 4); the plan starts with its
+ *                               own choice for its ring and column counts
  *   SC_PARAM_SKY_LMAX           band limit of the layout of the alm array given to
  *                               sc_set_sky_beam (>= lmax; a shared sky may have a larger one)
  *   SC_PARAM_GATHER_WAVES       waves per workgroup of the SC_MMA_FP32 gather, 4 or 8 (default 4);

@@ -246,9 +246,9 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
 
 template <typename FT, bool TAB>
 static void launch_ring_sums(sc_plan *p, const double *alm, const double *blm, FT *F) {
-    const int nblk = (p->lmax + 1) * (p->kmax + 1) * p->ngroups_run;
+    const int nblk = (p->lmax + 1) * (p->kmax + 1) * p->ngroups;
     auto kern = k_ring_sums<4, FT, TAB>;
-    switch (p->rpt_run) {
+    switch (p->rpt) {  // (4 here; there is no 6, nowhere better than 3)
         case 1: kern = k_ring_sums<1, FT, TAB>; break;
         case 2: kern = k_ring_sums<2, FT, TAB>; break;
         case 3: kern = k_ring_sums<3, FT, TAB>; break;
@@ -260,7 +260,7 @@ static void launch_ring_sums(sc_plan *p, const double *alm, const double *blm, F
     }
     hipLaunchKernelGGL(kern, dim3(nblk), dim3(64), 0, p->stream, (const double2 *)alm, (const double2 *)blm, F,
                        p->sbin_m, p->sbin_e, p->rtab, p->rroot, p->ctab, p->ctab_off, p->lmax, p->kmax, p->nring,
-                       p->ngroups_run, p->alm_lmax);
+                       p->ngroups, p->alm_lmax);
 }
 
 hipError_t sc_launch_ring_sums(sc_plan *p, const double *alm, const double *blm) {
@@ -318,7 +318,7 @@ int sc_ring_groups(int nring, int rpt) {
 // (more independent recursions per wave hide the FMA latency) up to 3, where the
 // kernel still runs three waves per SIMD: relative costs 1.65, 1.14, 1.0, 0.97 for
 // 1 .. 4.  The layout minimises slots x cost.
-void sc_choose_ring_layout(int nring, int *rpt, int *ngroups) {
+void sc_choose_ring_layout_short(int nring, int *rpt, int *ngroups) {
     static const double cost[5] = {0.0, 1.65, 1.14, 1.0, 0.97};
     int best_r = 3, best_g = sc_ring_groups(nring, 3);
     double best = 1e300;
@@ -342,7 +342,7 @@ void sc_choose_ring_layout(int nring, int *rpt, int *ngroups) {
     *ngroups = best_g;
 }
 
-// Layout the FP64 kernel runs with when none is set: up to nine rings per lane.  A longer
+// Layout of the FP64 kernel: up to nine rings per lane.  A longer
 // lane wastes fewer slots at some ring counts (lmax 384: 224 slots at 7 a lane, 256 at 4) and
 // shares the coefficients of a chunk among more recursions; per slot, 4 and more cost the
 // same within a few percent.  lmax 384, kmax 45: 455 us at 4, 407 at 7; lmax 2500, kmax 4:
@@ -350,9 +350,9 @@ void sc_choose_ring_layout(int nring, int *rpt, int *ngroups) {
 // than 3).  It also leaves fewer waves, so more than 4 only where four waves a SIMD remain:
 // lmax 512 with 9 a lane, 5643 waves: 449 us a pass against 464 with 3, with 3078 waves 299
 // against 280.
-void sc_choose_ring_layout_run(int nring, int ncol, int *rpt, int *ngroups) {
+void sc_choose_ring_layout(int nring, int ncol, int *rpt, int *ngroups) {
     static const double cost[10] = {0.0, 1.65, 1.12, 1.0, 0.985, 0.97, 0.0, 0.985, 0.97, 0.97};
-    sc_choose_ring_layout(nring, rpt, ngroups);
+    sc_choose_ring_layout_short(nring, rpt, ngroups);
     double best = (double)*ngroups * *rpt * cost[*rpt];
     for (int r = 5; r <= 9; ++r) {
         const int g = sc_ring_groups(nring, r);

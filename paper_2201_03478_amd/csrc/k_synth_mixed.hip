@@ -247,4 +247,4 @@ hipError_t sc_launch_ring_sums_mixed(sc_plan *p, const double *alm, const double
 }
 
 // The same layout as the FP64 kernel (32 northern rings per recursion and lane slot).
-void sc_choose_ring_layout_mixed(int nring, int *rpt, int *ngroups) { sc_choose_ring_layout(nring, rpt, ngroups); }
+void sc_choose_ring_layout_mixed(int nring, int *rpt, int *ngroups) { sc_choose_ring_layout_short(nring, rpt, ngroups); }

@@ -502,8 +502,7 @@ int sc_plan_create(sc_plan **out, int lmax, int kmax, int precision, int kernel_
         long long v = b ? std::atoll(b) : 0;
         p->bin_pass_max = (v > 0 && v < BIN_PASS_MAX) ? (int64_t)v : (int64_t)BIN_PASS_MAX;
     }
-    sc_choose_ring_layout(p->nring, &p->rpt, &p->ngroups_run);
-    sc_choose_ring_layout_run(p->nring, (p->lmax + 1) * (p->kmax + 1), &p->rpt_run, &p->ngroups_run);
+    sc_choose_ring_layout(p->nring, (p->lmax + 1) * (p->kmax + 1), &p->rpt, &p->ngroups);
     sc_choose_ring_layout_mixed(p->nring, &p->rpt_mx, &p->ngroups_mx);
     // whole transforms fill the LDS (160 KB) at 10240 points; the split stages hold 9216
     const int longest = std::max(p->n2os, p->nphi);
@@ -1106,18 +1105,15 @@ int sc_plan_set_param(sc_plan *p, int param, int64_t v) {
             p->gather_mma = (int)v;
             return SC_OK;
         case SC_PARAM_RING_RPT: {
-            if (v < 1 || v > 4) return fail(SC_EINVAL, "rings per lane %lld outside [1, 4]", (long long)v);
             if (p->prec == SC_MIXED) {
+                if (v < 1 || v > 4) return fail(SC_EINVAL, "rings per lane %lld outside [1, 4]", (long long)v);
                 p->rpt_mx = (int)v;
                 p->ngroups_mx = sc_ring_groups(p->nring, (int)v);
             } else {
-                // the value the plan started with stands for its own choice of layout
-                int def, ng;
-                sc_choose_ring_layout(p->nring, &def, &ng);
-                p->rpt = p->rpt_run = (int)v;
-                p->ngroups_run = sc_ring_groups(p->nring, (int)v);
-                if (v == def)
-                    sc_choose_ring_layout_run(p->nring, (p->lmax + 1) * (p->kmax + 1), &p->rpt_run, &p->ngroups_run);
+                if (v < 1 || v > 9 || v == 6)
+                    return fail(SC_EINVAL, "rings per lane %lld is not one of 1 to 5 and 7 to 9", (long long)v);
+                p->rpt = (int)v;
+                p->ngroups = sc_ring_groups(p->nring, (int)v);
             }
             return SC_OK;
         }

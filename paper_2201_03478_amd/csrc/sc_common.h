@@ -123,8 +123,7 @@ struct sc_plan {
     int nphi;          // oversampled phi grid, spacing 2 pi / nphi
     int rows, cols;    // stored map rows (theta nodes incl. ghost rows) and columns (incl. wrap)
     int ncomp, ncp;    // 2 kmax + 2 stored components (cos/sin pairs), padded count
-    int rpt;           // SC_PARAM_RING_RPT of the FP64 recursion
-    int rpt_run, ngroups_run;  // its layout: rings per lane, ring groups per (k, m)
+    int rpt, ngroups;  // FP64 recursion layout: rings per lane, ring groups per (k, m)
     int rpt_mx, ngroups_mx;  // the same for the FP32 (mixed-precision) recursion
     hipStream_t stream;
     hipStream_t side;             // sc_plan_convolve: binning beside the map synthesis
@@ -247,8 +246,8 @@ hipError_t sc_launch_gather_psi(sc_plan *p, const double *ptg, int64_t n, void *
 int sc_psi_max_len();
 hipError_t sc_launch_ring_sums(sc_plan *p, const double *alm, const double *blm);
 hipError_t sc_launch_rec_table(sc_plan *p);  // fills ctab (after sc_launch_tables)
-void sc_choose_ring_layout(int nring, int *rpt, int *ngroups);
-void sc_choose_ring_layout_run(int nring, int ncol, int *rpt, int *ngroups);
+void sc_choose_ring_layout(int nring, int ncol, int *rpt, int *ngroups);  // ncol: (m, k) columns
+void sc_choose_ring_layout_short(int nring, int *rpt, int *ngroups);      // at most four rings per lane
 int sc_ring_groups(int nring, int rpt);  // ring groups of the FP64 ring-sum kernel
 hipError_t sc_launch_ring_sums_mixed(sc_plan *p, const double *alm, const double *blm);
 void sc_choose_ring_layout_mixed(int nring, int *rpt, int *ngroups);
