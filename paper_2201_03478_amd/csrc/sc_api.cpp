@@ -536,8 +536,9 @@ int sc_plan_create(sc_plan **out, int lmax, int kmax, int precision, int kernel_
     rc = rc ? rc : alloc((void **)&p->glx, sizeof(double) * p->nq, &tot);
     rc = rc ? rc : alloc((void **)&p->glw, sizeof(double) * p->nq, &tot);
     // Recursion coefficients of every (m, k, l) column for the ring-sum kernels (32 B per
-    // entry: 0.66 GB at lmax 512 / kmax 100, 3.2 GB at lmax 8192 / kmax 2); above 8 GiB the
-    // kernels compute them per chunk instead.
+    // entry: 0.66 GB at lmax 512 / kmax 100, 3.2 GB at lmax 8192 / kmax 2); above 8 GiB (or
+    // with SC_REC_TABLE=0 in the environment, a test hook) the kernels compute them per chunk
+    // instead.
     std::vector<long long> coff((size_t)(lmax + 1) * (kmax + 1));
     long long ctot = 0;
     for (int m = 0; m <= lmax; ++m)
@@ -545,7 +546,8 @@ int sc_plan_create(sc_plan **out, int lmax, int kmax, int precision, int kernel_
             coff[(size_t)m * (kmax + 1) + k] = ctot;
             ctot += lmax - (m > k ? m : k) + 1;
         }
-    if ((double)ctot * 32.0 <= 8.0 * (1 << 30)) {
+    const char *tab = std::getenv("SC_REC_TABLE");
+    if ((double)ctot * 32.0 <= 8.0 * (1 << 30) && !(tab && std::strcmp(tab, "0") == 0)) {
         rc = rc ? rc : alloc((void **)&p->ctab, 32 * (size_t)ctot, &tot);
         rc = rc ? rc : alloc((void **)&p->ctab_off, sizeof(long long) * coff.size(), &tot);
     }

@@ -95,7 +95,8 @@ __device__ __forceinline__ void rec_coefs(int l, double mm, double kk, double mk
 // bn = (alpha_l + beta_l) S_l / S_{l+1} for the column (-m, k) (R-).  alpha, beta
 // and gamma come from the plan's root table sqrt((l+1)^2 - x^2) and its
 // reciprocal; S_l from a product scan over the lanes of each parity, carried
-// across chunks in s_prev = S_{lc-1}, s_cur = S_{lc}.  Called by all 64 lanes.
+// across chunks in s_prev = S_{lc-1}, s_cur = S_{lc}.  Called by all 64 lanes.  Zero past
+// lmax, where the steps of a last, rounded-up group run on.
 struct ChunkCoef {
     double a, b, bn, sl;  // sl = S_l, the factor of the contraction weights
 };
@@ -138,6 +139,7 @@ __device__ __forceinline__ ChunkCoef chunk_coefs(int lc, int lane, int l0, int l
     if (lane == 0) Sl = s_cur;
     s_prev = __shfl(T, 62);  // S_{lc+63} and S_{lc+64} for the next chunk
     s_cur = __shfl(T, 63);
+    if (l > lmax) return ChunkCoef{0.0, 0.0, 0.0, 0.0};
     const double ratio = Sl / T;
     return ChunkCoef{A * ratio, B * ratio, Bn * ratio, Sl};
 }
@@ -146,7 +148,7 @@ __device__ __forceinline__ ChunkCoef chunk_coefs(int lc, int lane, int l0, int l
 // column (k_rec_table, entry l - l0 of column (m, k) = (a, b, bn, S_l) as chunk_coefs
 // returns them, with the same chunking from l0): one coalesced load per lane instead
 // of the root-table loads, two divisions and the product scan, in every wave of every
-// synthesis.  Zero past lmax (no step reads those; the weights there are zero).
+// synthesis.  Zero past lmax, as chunk_coefs.
 __device__ __forceinline__ ChunkCoef chunk_coefs_tab(const double4 *__restrict__ col, int lc, int lane, int l0,
                                                      int lmax) {
     const int l = lc + lane;
