@@ -108,8 +108,17 @@ __device__ __forceinline__ void rec_step(const RecCoef &c, const double *x, doub
 
 // One loop over the steps, fast or scaled: with separate loops the compiler kept the rings'
 // state in two sets of registers (166 at 3 rings per lane, 122 with one loop; spills past 5).
-template <int RPT, typename FT, bool TAB>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RPT <= 3 ? 3 : 2)))
+// FEW: no more waves a SIMD than that bound asks for, for launches of a few waves per SIMD.
+// With all of them resident from the start a SIMD keeps the columns it was given, whose lengths
+// fall from lmax to one step, and the longest set decides; otherwise the rest go where a SIMD
+// falls free (lmax 1000, kmax 0, 4004 waves: 139 us all resident, 123 so; lmax 384, kmax 3,
+// 3080 waves: 51 and 45).  From 7000 waves on more of them hide more (lmax 200, kmax 100,
+// 20301 waves: 137 us against 147 so; the line lies between 6606 and 6930 waves).
+constexpr int RING_FEW = 6656;
+constexpr int ring_waves(int rpt) { return rpt <= 3 ? 3 : 2; }
+template <int RPT, typename FT, bool TAB, bool FEW>
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(ring_waves(RPT), FEW ? ring_waves(RPT) : 8)))
 k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT *__restrict__ F,
             const double *__restrict__ sbin_m, const int *__restrict__ sbin_e,
             const double *__restrict__ rtab, const double2 *__restrict__ rroot, const double4 *__restrict__ ctab,
@@ -186,23 +195,27 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
         // to the same registers, so neither the loads nor the recursion need register moves.
         // The last chunk is rounded up to whole iterations: steps past lmax have zero
         // weights and coefficients.
-        // Rescaling is checked once per 32 steps: one step grows |u| by at most
-        // ~2^11, so 32 steps stay inside the 2^424 left below overflow, and what a
-        // ring accumulates between passing 2^600 and its rescale (true values below
+        // Rescaling is checked once per 32 steps, outside their loop (a check in every iteration
+        // costs launches of few waves 5%: lmax 256, kmax 0: 22.7 against 21.6 us): one step
+        // grows |u| by at most ~2^11, so 32 steps stay inside the 2^424 left below overflow,
+        // and what a ring accumulates between passing 2^600 and its rescale (true values below
         // 2^{-600 + 352}) is dropped harmlessly with the scaled sums.
         RecCoef a0 = rec_load(0, cA, cBt, cWp, cWm), a1 = rec_load(1, cA, cBt, cWp, cWm);
-        for (int t = 0; t < nl; t += 4) {
-            const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
-            __builtin_amdgcn_sched_barrier(0);
-            rec_step<RPT>(a0, x, u, up, fp, fm);
-            rec_step<RPT>(a1, x, u, up, fp, fm);
-            const int tn = (t + 4) & 63;  // last iteration: harmless re-read
-            a0 = rec_load(tn, cA, cBt, cWp, cWm);
-            a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
-            __builtin_amdgcn_sched_barrier(0);
-            rec_step<RPT>(b0, x, u, up, fp, fm);
-            rec_step<RPT>(b1, x, u, up, fp, fm);
-            if (fast || ((t & 28) != 28 && t + 4 < nl)) continue;
+        for (int t0 = 0; t0 < nl; t0 += 32) {
+            const int t1 = t0 + 32 < nl ? t0 + 32 : nl;
+            for (int t = t0; t < t1; t += 4) {
+                const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
+                __builtin_amdgcn_sched_barrier(0);
+                rec_step<RPT>(a0, x, u, up, fp, fm);
+                rec_step<RPT>(a1, x, u, up, fp, fm);
+                const int tn = (t + 4) & 63;  // last iteration: harmless re-read
+                a0 = rec_load(tn, cA, cBt, cWp, cWm);
+                a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
+                __builtin_amdgcn_sched_barrier(0);
+                rec_step<RPT>(b0, x, u, up, fp, fm);
+                rec_step<RPT>(b1, x, u, up, fp, fm);
+            }
+            if (fast) continue;
             bool low = false;
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
@@ -247,15 +260,16 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
 template <typename FT, bool TAB>
 static void launch_ring_sums(sc_plan *p, const double *alm, const double *blm, FT *F) {
     const int nblk = (p->lmax + 1) * (p->kmax + 1) * p->ngroups;
-    auto kern = k_ring_sums<4, FT, TAB>;
-    switch (p->rpt) {  // (4 here; there is no 6, nowhere better than 3)
-        case 1: kern = k_ring_sums<1, FT, TAB>; break;
-        case 2: kern = k_ring_sums<2, FT, TAB>; break;
-        case 3: kern = k_ring_sums<3, FT, TAB>; break;
-        case 5: kern = k_ring_sums<5, FT, TAB>; break;
-        case 7: kern = k_ring_sums<7, FT, TAB>; break;
-        case 8: kern = k_ring_sums<8, FT, TAB>; break;
-        case 9: kern = k_ring_sums<9, FT, TAB>; break;
+    const bool few = nblk <= RING_FEW;
+    auto kern = few ? k_ring_sums<4, FT, TAB, true> : k_ring_sums<4, FT, TAB, false>;
+    switch (p->rpt) {  // (4 here; there is no 6, nowhere better than 3; from 5 on the registers allow two waves)
+        case 1: kern = few ? k_ring_sums<1, FT, TAB, true> : k_ring_sums<1, FT, TAB, false>; break;
+        case 2: kern = few ? k_ring_sums<2, FT, TAB, true> : k_ring_sums<2, FT, TAB, false>; break;
+        case 3: kern = few ? k_ring_sums<3, FT, TAB, true> : k_ring_sums<3, FT, TAB, false>; break;
+        case 5: kern = k_ring_sums<5, FT, TAB, true>; break;
+        case 7: kern = k_ring_sums<7, FT, TAB, true>; break;
+        case 8: kern = k_ring_sums<8, FT, TAB, true>; break;
+        case 9: kern = k_ring_sums<9, FT, TAB, true>; break;
         default: break;
     }
     hipLaunchKernelGGL(kern, dim3(nblk), dim3(64), 0, p->stream, (const double2 *)alm, (const double2 *)blm, F,
