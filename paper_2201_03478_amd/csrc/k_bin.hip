@@ -12,8 +12,8 @@
 //   k_bin_scatter  sample records in key order: fractional offsets and psi
 //                  (FP64) and the original index, 32 bytes each
 //   k_bin_items    work items (key, first sorted sample, count <= the plan's bin chunk);
-//                  for the split gather, anchors of at most BIN_SHORT samples are listed
-//                  apart, from the end of the item array down
+//                  anchors of at most BIN_SHORT samples for the split gather, BIN_SHORT_SC64
+//                  for the FP64 scatter, are listed apart, from the end of the item array down
 //   k_bin_small    all of it in one workgroup, for passes of at most BIN_SMALL samples
 //
 // Integer index arithmetic is exact; the fractional offsets u - floor(u) are
@@ -265,28 +265,64 @@ __global__ void k_bin_scatter(const double *__restrict__ ptg, int64_t n, BinGeom
     }
 }
 
-__global__ void k_bin_items(const int *__restrict__ count, const int2 *__restrict__ offs, int64_t nkeys,
-                            int4 *__restrict__ items, int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = k < nkeys ? count[k] : 0;
-    if (shortn > 0) {
-        // one reservation per wave, so neighbouring anchors stay neighbours in the list
-        const bool is = c > 0 && c <= shortn;
-        const unsigned long long mask = __ballot(is);
-        const int lane = threadIdx.x & 63;
-        int base = 0;
-        if (mask && lane == 0) base = atomicAdd(&totals[3], __popcll(mask));
-        base = __shfl(base, 0);
-        if (is) {
-            const int i = base + __popcll(mask & ((1ull << lane) - 1));
-            items[cap - 1 - i] = make_int4((int)k, offs[k].x, c, 0);
-        }
+// A workgroup lists 256 PER anchors; the short ones among them get one reservation, so
+// neighbouring anchors stay neighbours and the counter sees one atomic per workgroup (8 ns each:
+// with one per wave of 64 anchors they took 0.35 ms of a pass of 1e5 uniform pointings at lmax
+// 512).  From 2^20 anchors on PER = 16; below 4, so that the workgroups still fill the chip.
+constexpr int ITEMS_NT = 256;
+template <int ITEMS_PER>
+__global__ void __launch_bounds__(ITEMS_NT)
+k_bin_items(const int *__restrict__ count, const int2 *__restrict__ offs, int64_t nkeys, int4 *__restrict__ items,
+            int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
+    constexpr int NWV = ITEMS_NT / 64;
+    static_assert(NWV * ITEMS_PER <= 64, "one wave scans the counts of every wave and step");
+    __shared__ int before[NWV * ITEMS_PER];  // short anchors ahead of a wave's step
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t k0 = (int64_t)blockIdx.x * (ITEMS_NT * ITEMS_PER) + threadIdx.x;
+    int c[ITEMS_PER];
+#pragma unroll
+    for (int q = 0; q < ITEMS_PER; ++q) {
+        const int64_t k = k0 + q * ITEMS_NT;
+        c[q] = k < nkeys ? count[k] : 0;
     }
-    if (c <= shortn) return;
-    const int2 o = offs[k];
-    for (int q = 0; q * chunk < c; ++q) {
-        const int cnt = c - q * chunk < chunk ? c - q * chunk : chunk;
-        items[o.y + q] = make_int4((int)k, o.x + q * chunk, cnt, 0);
+    if (shortn > 0) {
+#pragma unroll
+        for (int q = 0; q < ITEMS_PER; ++q) {
+            const unsigned long long mask = __ballot(c[q] > 0 && c[q] <= shortn);
+            if (lane == 0) before[q * NWV + wv] = __popcll(mask);
+        }
+        __syncthreads();
+        if (wv == 0) {
+            const int n = lane < NWV * ITEMS_PER ? before[lane] : 0;
+            int incl = n;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int t = __shfl_up(incl, off);
+                if (lane >= off) incl += t;
+            }
+            int base = 0;
+            if (lane == 63 && incl > 0) base = atomicAdd(&totals[3], incl);
+            base = __shfl(base, 63);
+            if (lane < NWV * ITEMS_PER) before[lane] = base + incl - n;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < ITEMS_PER; ++q) {
+        const int64_t k = k0 + q * ITEMS_NT;
+        const bool is = c[q] > 0 && c[q] <= shortn;
+        const unsigned long long mask = __ballot(is);
+        if (c[q] == 0) continue;
+        const int2 o = offs[k];
+        if (is) {
+            items[cap - 1 - (before[q * NWV + wv] + __popcll(mask & ((1ull << lane) - 1)))] =
+                make_int4((int)k, o.x, c[q], 0);
+        } else {
+            for (int i = 0; i * chunk < c[q]; ++i) {
+                const int cnt = c[q] - i * chunk < chunk ? c[q] - i * chunk : chunk;
+                items[o.y + i] = make_int4((int)k, o.x + i * chunk, cnt, 0);
+            }
+        }
     }
 }
 
@@ -304,6 +340,10 @@ constexpr int SMALL_HPT = SMALL_HT / SMALL_NT;
 __global__ void __launch_bounds__(SMALL_NT)
 k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, const float *__restrict__ y,
             int4 *__restrict__ items, int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
+    // the short list takes every item (the split gather, chunk = shortn), or the anchors of at
+    // most shortn samples
+    const bool all_short = shortn > 0 && chunk == shortn;
+    __shared__ int nshort;
     __shared__ int hkey[SMALL_HT];
     __shared__ int hcnt[SMALL_HT];  // samples of the slot's key, then its first record
     __shared__ unsigned sh[SMALL_NT / 64];
@@ -313,6 +353,7 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
         hkey[tid + i * SMALL_NT] = KEYS_EMPTY;
         hcnt[tid + i * SMALL_NT] = 0;
     }
+    if (tid == 0) nshort = 0;
     double fu[SMALL_SPT], fv[SMALL_SPT], psi[SMALL_SPT];
     int key[SMALL_SPT], slot[SMALL_SPT], rank[SMALL_SPT];
 #pragma unroll
@@ -346,7 +387,8 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
 #pragma unroll
     for (int i = 0; i < SMALL_HPT; ++i) {
         const int c = hcnt[SMALL_HPT * tid + i];
-        v[i] = ((unsigned)((c + chunk - 1) / chunk) << 16) | (unsigned)c;
+        const int listed = !all_short && c <= shortn ? 0 : (c + chunk - 1) / chunk;
+        v[i] = ((unsigned)listed << 16) | (unsigned)c;
         sum += v[i];
     }
     unsigned incl = sum;
@@ -365,20 +407,23 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
         if (c) {
             const int k = hkey[SMALL_HPT * tid + i];
             hcnt[SMALL_HPT * tid + i] = first;
-            for (int q = 0; q * chunk < c; ++q)
-                items[shortn > 0 ? cap - 1 - (it + q) : it + q] =
-                    make_int4(k, first + q * chunk, c - q * chunk < chunk ? c - q * chunk : chunk, 0);
+            if (!all_short && c <= shortn)
+                items[cap - 1 - atomicAdd(&nshort, 1)] = make_int4(k, first, c, 0);
+            else
+                for (int q = 0; q * chunk < c; ++q)
+                    items[all_short ? cap - 1 - (it + q) : it + q] =
+                        make_int4(k, first + q * chunk, c - q * chunk < chunk ? c - q * chunk : chunk, 0);
         }
         run += v[i];
     }
+    __syncthreads();
     if (tid == SMALL_NT - 1) {
         const int nit = (int)(run >> 16);
         totals[0] = n;
-        totals[1] = shortn > 0 ? 0 : nit;
+        totals[1] = all_short ? 0 : nit;
         totals[2] = 0;
-        totals[3] = shortn > 0 ? nit : 0;
+        totals[3] = all_short ? nit : nshort;
     }
-    __syncthreads();
 #pragma unroll
     for (int q = 0; q < SMALL_SPT; ++q) {
         if (key[q] < 0) continue;
@@ -440,12 +485,15 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     const unsigned gs = (unsigned)((n + bs - 1) / bs);
     int chunk = p->bin_chunk;
     if (p->prec == SC_FP64) chunk = std::min(chunk, use == SC_BIN_SCATTER ? BIN_CHUNK_SC64 : BIN_CHUNK_64);
-    const int shortn = use == SC_BIN_GATHER && sc_short_items(p, n) ? BIN_SHORT : 0;
+    const int shortn = use == SC_BIN_GATHER && sc_short_items(p, n) ? BIN_SHORT
+                       : use == SC_BIN_SCATTER && sc_short_items64(p) ? BIN_SHORT_SC64
+                                                                      : 0;
     // (the deterministic scatter reads the per-anchor tables of the general path)
     w.small = n <= BIN_SMALL && !(use == SC_BIN_SCATTER && p->det_adjoint);
     if (w.small) {
         hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg, (int)n, g, w.sorted, y, w.items,
-                           shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap, w.totals);
+                           use == SC_BIN_GATHER && shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap,
+                           w.totals);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
@@ -459,7 +507,8 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, w.offs, chunk,
                        shortn);
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
-    hipLaunchKernelGGL(k_bin_items, dim3((unsigned)((nkeys + bs - 1) / bs)), dim3(bs), 0, p->stream, w.count,
+    const int64_t per = ITEMS_NT * (nkeys >= (1 << 20) ? 16 : 4);
+    hipLaunchKernelGGL(nkeys >= (1 << 20) ? k_bin_items<16> : k_bin_items<4>, dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count,
                        w.offs, nkeys, w.items, chunk, shortn, w.cap, w.totals);
     return hipGetLastError();
 }

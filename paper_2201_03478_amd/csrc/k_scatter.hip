@@ -16,9 +16,13 @@
 //    weight w_s(t) = w_theta(t / 8) w_phi(t % 8) is formed from the 1-d weights
 //    in LDS as the matrix operand is read.  The atomics are not what limits it:
 //    without them the kernel takes within 2% of the time.
-//  * k_scatter_mfma64 (FP64 maps): the same product in FP64 for every even W.
-//  * k_scatter_direct (FP32 maps with W != 8, and the forced per-sample path): one wave
-//    per sample, lanes over components, one atomic per (tap, component, sample).
+//  * k_scatter_mfma64 (FP64 maps): the same product in FP64 for every even W; anchors of at
+//    most four samples go to k_scatter_short64, one wave each.
+//  * k_scatter_direct (FP32 maps with W != 8; FP64 passes too small to pay for the binning, or
+//    without its workspace; the forced per-sample path): one wave per sample, lanes over
+//    components, one atomic per (tap, component, sample).
+#include <algorithm>
+
 #include "sc_common.h"
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -547,15 +551,101 @@ k_scatter_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals,
     }
 }
 
+// Anchors of at most BIN_SHORT_SC64 samples, one wave each: the sum over the samples in
+// registers, one atomic per (tap, component), 64 of them at a time (CW components of 64 / CW
+// taps).  The matrix form costs such an item its barriers and LDS fills, about as much as the
+// atomics of four samples: 1e5 uniform pointings, W = 14, lmax 512, kmax 0: 1.70 ms with it,
+// 0.50 here, 0.92 sample by sample; kmax 8: 3.2, 2.4 and 2.6.
+template <int W, int NS, int CW>
+__device__ __forceinline__ void scatter64_samples(const BinRec *__restrict__ rc, int ns, const double *__restrict__ y,
+                                                  double *__restrict__ gm, int cols, int ncp, int ncomp, double beta,
+                                                  int lane) {
+    constexpr int TP = 64 / CW;  // taps at a time
+    double w[NS], ys[NS];
+    double2 e1[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        w[s] = ys[s] = 0.0;
+        e1[s] = make_double2(0.0, 0.0);
+        if (s < ns) {
+            const BinRec q = rc[s];
+            sincos(q.psi, &e1[s].y, &e1[s].x);
+            ys[s] = y[q.idx];
+            const bool th = lane < W;
+            if (lane < 2 * W)
+                w[s] = es_w<double>(((th ? q.fu : q.fv) + (double)(W / 2 - 1 - (th ? lane : lane - W))) / (double)(W / 2),
+                                    beta);
+        }
+    }
+    for (int c0 = 0; c0 < ncomp; c0 += CW) {
+        const int c = c0 + lane % CW;
+        double val[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const double2 z = cpow_int(e1[s], c >> 1);
+            val[s] = ys[s] * ((c & 1) ? z.y : z.x);
+        }
+        const bool on = c < ncomp && c != 1;  // basis_1 = sin 0 = 0
+#pragma unroll 2
+        for (int t0 = 0; t0 < W * W; t0 += TP) {
+            const int t = t0 + lane / CW, i = t / W, j = t - i * W;
+            double a = 0.0;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) a = fma(__shfl(w[s], i) * __shfl(w[s], W + j), val[s], a);
+            if (on && t < W * W) atomic_add(gm + ((size_t)i * cols + j) * ncp + c, a);
+        }
+    }
+}
+template <int W, int NS>
+__device__ __forceinline__ void scatter64_short(const BinRec *__restrict__ rc, int ns, const double *__restrict__ y,
+                                                double *__restrict__ gm, int cols, int ncp, int ncomp, double beta,
+                                                int lane) {
+    if (ncomp <= 4)
+        scatter64_samples<W, NS, 4>(rc, ns, y, gm, cols, ncp, ncomp, beta, lane);
+    else if (ncomp <= 16)
+        scatter64_samples<W, NS, 16>(rc, ns, y, gm, cols, ncp, ncomp, beta, lane);
+    else
+        scatter64_samples<W, NS, 32>(rc, ns, y, gm, cols, ncp, ncomp, beta, lane);
+}
+
+template <int W>
+__global__ void __launch_bounds__(256)
+k_scatter_short64(const int4 *__restrict__ items, const int *__restrict__ totals, int64_t cap,
+                  const BinRec *__restrict__ rec, const double *__restrict__ y, double *__restrict__ gmaps, int cols,
+                  int ncp, int ncomp, int nkc, double beta) {
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nitems = totals[3];
+    for (int it = xcd_remap(blockIdx.x, gridDim.x) * 4 + wv; it < nitems; it += gridDim.x * 4) {
+        const int4 item = items[cap - 1 - it];
+        const int row0 = item.x / nkc, col0 = item.x - (item.x / nkc) * nkc;
+        double *gm = gmaps + ((size_t)row0 * cols + col0) * ncp;
+        const BinRec *rc = rec + item.y;
+        if (item.z == 1)
+            scatter64_short<W, 1>(rc, 1, y, gm, cols, ncp, ncomp, beta, lane);
+        else if (item.z == 2)
+            scatter64_short<W, 2>(rc, 2, y, gm, cols, ncp, ncomp, beta, lane);
+        else
+            scatter64_short<W, BIN_SHORT_SC64>(rc, item.z, y, gm, cols, ncp, ncomp, beta, lane);
+    }
+}
+
 template <int W>
 hipError_t launch_scatter_mfma64(sc_plan *p, const double *y, double *gmaps) {
+    const int nkc = sc_bin_geom(p).nkc;
+    if (sc_short_items64(p)) {
+        auto shrt = k_scatter_short64<W>;
+        const int sgrid = (int)std::min<int64_t>(sc_persistent_grid((const void *)shrt, 256, 0, 0), (p->bw.last_n + 3) / 4);
+        hipLaunchKernelGGL(shrt, dim3(sgrid), dim3(256), 0, p->stream, p->bw.items, p->bw.totals, p->bw.cap,
+                           p->bw.sorted.rec, y, gmaps, p->cols, p->ncp, p->ncomp, nkc, p->beta);
+    }
     const size_t lds = Sc64<W>::lds();
     auto kern = k_scatter_mfma64<W>;
     hipError_t e = sc_set_lds_attr((const void *)kern, lds);
     if (e != hipSuccess) return e;
     const int grid = sc_persistent_grid((const void *)kern, 256, lds, p->gather_wgs_per_cu);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, p->stream, p->bw.items, p->bw.totals, p->bw.sorted.rec, y, gmaps,
-                       p->cols, p->ncp, p->ncomp, sc_bin_geom(p).nkc, p->beta);
+                       p->cols, p->ncp, p->ncomp, nkc, p->beta);
     return hipGetLastError();
 }
 
@@ -759,6 +849,20 @@ hipError_t sc_launch_scatter_reduce(sc_plan *p, void *gmaps) {
 // FP64 plans: the binned scatter of one pass (after sc_launch_binning in adjoint form without y).
 bool sc_scatter64_supported(const sc_plan *p) {
     return p->prec == SC_FP64 && p->W >= 4 && p->W <= 16 && (p->W & 1) == 0 && p->ncomp <= 256 && !p->gather_direct;
+}
+// Whether binning a pass of n samples pays.  Sample by sample the scatter is bound by its
+// atomics, one request per tap and 64-byte sector of a pixel's components at 45 ps (W = 14, 2e4
+// to 4e5 samples: 8.8 ns a sample up to kmax 3, 17 up to 7, 26 at 8, 53 at 20; W = 8: 3.3).  The
+// binning costs a launch of 12 us up to BIN_SMALL samples, from there its seven kernels and
+// 10.5 ps per anchor (34 us at lmax 64, 56 at 512, 132 at 1024), and only samples that share
+// anchors give it back: spread evenly, the same atomics remain.  So it runs where it is at most
+// half of the per-sample form's time.  Near the line, lmax 64, kmax 4, 5000 samples: uniform
+// 113 us sample by sample and 118 binned, scan 145 and 74.
+bool sc_scatter64_pays(const sc_plan *p, int64_t n) {
+    const BinGeom g = sc_bin_geom(p);
+    const double direct = 45e-6 * (double)n * p->W * p->W * ((p->ncomp + 7) / 8);
+    const double bin = n <= BIN_SMALL ? 12.0 : 34.0 + 10.5e-6 * (double)g.nkr * (double)g.nkc;
+    return direct > 2.0 * bin;
 }
 hipError_t sc_launch_scatter64(sc_plan *p, const double *y, double *gmaps) {
     switch (p->W) {

@@ -998,10 +998,10 @@ static int adjoint_to_rings(sc_plan *p, const double *ptg, const void *tod_grad,
                 off += cnt;
             }
         } else {
-            // FP64: binned on the matrix cores; sample by sample if the binning workspace cannot
-            // be had (or the plan takes the per-sample path)
+            // FP64: binned on the matrix cores; sample by sample if the binning would not pay or
+            // its workspace cannot be had (or the plan takes the per-sample path)
             const int64_t pass = std::min<int64_t>(n, std::min<int64_t>(p->bin_pass_max, BIN_PASS_ADJ64));
-            const bool binned = sc_scatter64_supported(p) && ensure_adj_bin_work(p, pass);
+            const bool binned = sc_scatter64_supported(p) && sc_scatter64_pays(p, pass) && ensure_adj_bin_work(p, pass);
             if (binned) {
                 const AdjBinScope scope(p);
                 for (int64_t off = 0; off < n; off += pass) {

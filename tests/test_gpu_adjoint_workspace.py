@@ -47,7 +47,7 @@ def test_adjoint_captured_above_the_workspace_it_has(n):
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
         plan = api.Plan(L, K, "fp64")
-        out = plan.adjoint(b, p[:100].clone(), y[:100].clone())
+        out = plan.adjoint(b, p[:2900].clone(), y[:2900].clone())
         g = _captured(s, lambda: plan.adjoint(b, p, y, out=out))
         ref = api.Plan(L, K, "fp64").adjoint(b, p, y)
         for m in (200, 5000, 50_000):
@@ -102,14 +102,18 @@ def test_interpolation_graph_survives_a_larger_adjoint():
             assert torch.equal(tod, ref)
 
 
-@pytest.mark.parametrize("n", [700, 701, 6000, 13_001])
-def test_adjoint_in_several_passes(monkeypatch, n):
+@pytest.mark.parametrize("limit,n,passes", [(3000, 3000, 1), (3000, 3001, 2), (3000, 9000, 3), (9000, 27_001, 4)])
+def test_adjoint_in_several_passes(monkeypatch, limit, n, passes):
+    """Passes of up to 3000 samples (one workgroup bins them) and of 9000 (the general path)."""
     a, b, p, y = _inputs(n)
     one = api.Plan(L, K, "fp64")
-    monkeypatch.setenv("SC_BIN_PASS_MAX", "700" if n < 10_000 else "5000")
+    monkeypatch.setenv("SC_BIN_PASS_MAX", str(limit))
     several = api.Plan(L, K, "fp64")
     monkeypatch.delenv("SC_BIN_PASS_MAX")
-    assert _close(several.adjoint(b, p, y), one.adjoint(b, p, y))
+    several.enable_timing(True)
+    got = several.adjoint(b, p, y)
+    assert several.stage_times()["binning"][1] == passes
+    assert _close(got, one.adjoint(b, p, y))
     assert _close(several.adjoint_beam(a, p, y), one.adjoint_beam(a, p, y))
 
 
