@@ -8,7 +8,7 @@
 //
 //   k_bin_keys     anchor key and rank within the key per sample (counts
 //                  aggregated per workgroup in LDS, one global atomic per key)
-//   k_scan_*       exclusive scan of (samples, work items) per key
+//   k_scan_*       exclusive scan of (samples, work items) per key, in two or three kernels
 //   k_bin_scatter  sample records in key order: fractional offsets and psi
 //                  (FP64) and the original index, 32 bytes each
 //   k_bin_items    work items (key, first sorted sample, count <= the plan's bin chunk);
@@ -137,28 +137,41 @@ __device__ __forceinline__ int2 key_pair(const int *count, int64_t i, int64_t nk
     return make_int2(c, c <= shortn ? 0 : (c + chunk - 1) / chunk);  // short anchors are listed apart
 }
 
-// block-wide exclusive scan of one int2 per thread; returns the block total
+// block-wide exclusive scan of one int2 per thread; returns the block total.  In registers
+// within a wave (through LDS with a barrier per step it took 2 us of a small scan's 7).
 __device__ int2 block_scan(int2 v, int2 *sh, int &excl_x, int &excl_y) {
-    const int tid = threadIdx.x;
-    sh[tid] = v;
-    __syncthreads();
-    for (int off = 1; off < SCAN_NT; off <<= 1) {
-        int2 t = tid >= off ? sh[tid - off] : make_int2(0, 0);
-        __syncthreads();
-        sh[tid] = make_int2(sh[tid].x + t.x, sh[tid].y + t.y);
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int2 incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int x = __shfl_up(incl.x, off), y = __shfl_up(incl.y, off);
+        if (lane >= off) {
+            incl.x += x;
+            incl.y += y;
+        }
     }
-    const int2 incl = sh[tid];
+    if (lane == 63) sh[wv] = incl;
+    __syncthreads();
+    int2 tot = make_int2(0, 0);
     excl_x = incl.x - v.x;
     excl_y = incl.y - v.y;
-    const int2 tot = sh[SCAN_NT - 1];
+#pragma unroll
+    for (int w = 0; w < SCAN_NT / 64; ++w) {
+        const int2 t = sh[w];
+        if (w < wv) {
+            excl_x += t.x;
+            excl_y += t.y;
+        }
+        tot.x += t.x;
+        tot.y += t.y;
+    }
     __syncthreads();
     return tot;
 }
 
 __global__ void __launch_bounds__(SCAN_NT) k_scan_reduce(const int *__restrict__ count, int64_t nkeys,
                                                          int2 *__restrict__ sums, int chunk, int shortn) {
-    __shared__ int2 sh[SCAN_NT];
+    __shared__ int2 sh[SCAN_NT / 64];
     const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + (int64_t)threadIdx.x * SCAN_PER;
     int2 acc = make_int2(0, 0);
     for (int q = 0; q < SCAN_PER; ++q) {
@@ -173,7 +186,7 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan_reduce(const int *__restrict__
 
 // single block: exclusive scan of the per-block sums; writes totals
 __global__ void __launch_bounds__(SCAN_NT) k_scan_sums(int2 *__restrict__ sums, int nblk, int *__restrict__ totals) {
-    __shared__ int2 sh[SCAN_NT];
+    __shared__ int2 sh[SCAN_NT / 64];
     int2 carry = make_int2(0, 0);
     for (int base = 0; base < nblk; base += SCAN_NT) {
         const int i = base + threadIdx.x;
@@ -192,10 +205,26 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan_sums(int2 *__restrict__ sums, 
     }
 }
 
+// OWN: sums are the per-block sums as k_scan_reduce left them; every block adds up those before
+// its own, the last one writes the totals, and k_scan_sums need not run (a launch of 4 us; with
+// up to SCAN_OWN blocks, 4.2e6 anchors, they read 8 KB each at most).
+constexpr int SCAN_OWN = 1024;
+template <bool OWN>
 __global__ void __launch_bounds__(SCAN_NT) k_scan_apply(const int *__restrict__ count, int64_t nkeys,
                                                         const int2 *__restrict__ sums, int2 *__restrict__ offs,
-                                                        int chunk, int shortn) {
-    __shared__ int2 sh[SCAN_NT];
+                                                        int chunk, int shortn, int *__restrict__ totals) {
+    __shared__ int2 sh[SCAN_NT / 64];
+    int2 bo = make_int2(0, 0);
+    if (OWN) {
+        for (int i = threadIdx.x; i < (int)blockIdx.x; i += SCAN_NT) {
+            bo.x += sums[i].x;
+            bo.y += sums[i].y;
+        }
+        int ex, ey;
+        bo = block_scan(bo, sh, ex, ey);
+    } else {
+        bo = sums[blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK + (int64_t)threadIdx.x * SCAN_PER;
     int2 v[SCAN_PER];
     int2 acc = make_int2(0, 0);
@@ -205,8 +234,13 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan_apply(const int *__restrict__ 
         acc.y += v[q].y;
     }
     int ex, ey;
-    block_scan(acc, sh, ex, ey);
-    const int2 bo = sums[blockIdx.x];
+    const int2 tot = block_scan(acc, sh, ex, ey);
+    if (OWN && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        totals[0] = bo.x + tot.x;
+        totals[1] = bo.y + tot.y;
+        totals[2] = 0;
+        totals[3] = 0;
+    }
     int2 run = make_int2(bo.x + ex, bo.y + ey);
     for (int q = 0; q < SCAN_PER; ++q) {
         if (base + q < nkeys) offs[base + q] = run;
@@ -329,7 +363,7 @@ k_bin_items(const int *__restrict__ count, const int2 *__restrict__ offs, int64_
 // A pass of at most BIN_SMALL samples in one workgroup: an LDS hash table of the keys gives
 // each sample its rank within its anchor, a scan over the slots the first record and work
 // item of each anchor, and the records and items follow.  (Anchors come in slot order, not
-// key order.)  The seven kernels of the general path cost a launch each, which is all that
+// key order.)  The six or seven kernels of the general path cost a launch each, which is all that
 // such a pass takes (1950 samples at lmax 256, interpolation with kmax 8: 66 us
 // through the general path, 18 us, 9 of them here).
 constexpr int SMALL_NT = 1024;
@@ -503,9 +537,10 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     hipLaunchKernelGGL(keys, dim3(gk), dim3(KEYS_NT), 0, p->stream, ptg, n, g, w.key, w.rank, w.count);
     const int nblk = (int)((nkeys + SCAN_BLOCK - 1) / SCAN_BLOCK);
     hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, chunk, shortn);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_NT), 0, p->stream, w.sums, nblk, w.totals);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count, nkeys, w.sums, w.offs, chunk,
-                       shortn);
+    const bool own = nblk <= SCAN_OWN;
+    if (!own) hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_NT), 0, p->stream, w.sums, nblk, w.totals);
+    hipLaunchKernelGGL(own ? k_scan_apply<true> : k_scan_apply<false>, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count,
+                       nkeys, w.sums, w.offs, chunk, shortn, w.totals);
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
     const int64_t per = ITEMS_NT * (nkeys >= (1 << 20) ? 16 : 4);
     hipLaunchKernelGGL(nkeys >= (1 << 20) ? k_bin_items<16> : k_bin_items<4>, dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count,

@@ -293,20 +293,6 @@ GatherDet sc_gather_det(const sc_plan *p, void *tod);
 hipError_t sc_launch_gather_batch(const GatherDet *dets_dev, int ndet, int max_ct, int *cursor, int wgs_per_cu, int waves,
                                   int mma, hipStream_t stream);
 bool sc_gather_binned_supported(const sc_plan *p);
-// Whether a gather pass of n samples lists its short items apart for k_gather_short (the
-// split form's FP32 maps).  That kernel splits the map block per wave, 16 ncomp values a
-// lane: with more than nine component tiles the workgroup form is the faster one for short
-// items too (1e5 uniform pointings at lmax 512, kmax 100: 2.25 against 2.46 ms; 2e5 at
-// lmax 256, kmax 64: 2.92 against 1.64 ms), unless the pass is too small to fill the chip
-// with workgroups (3000 scan samples at lmax 512, kmax 100: 113 against 53 us).
-static inline bool sc_short_items(const sc_plan *p, int64_t n) {
-    return p->prec != SC_FP64 && p->W == 8 && p->gather_mma == SC_MMA_SPLIT16 && !p->gather_valu &&
-           (n <= BIN_SMALL || p->ncomp <= 144);
-}
-// The same for the FP64 scatter: up to two component tiles (with more of them the wave form has
-// no more lanes to gain and the matrix form is as fast: kmax 20, lmax 256, 2e4 uniform samples
-// 1.20 against 1.31 ms, but kmax 127, lmax 128, 2e4 scan samples 485 against 341 us).
-static inline bool sc_short_items64(const sc_plan *p) { return p->prec == SC_FP64 && p->ncomp <= 32; }
 
 static inline BinGeom sc_bin_geom(const sc_plan *p) {
     const double two_pi = 6.283185307179586477;
@@ -319,6 +305,26 @@ static inline BinGeom sc_bin_geom(const sc_plan *p) {
     g.nkc = p->nphi;
     return g;
 }
+
+// Whether a gather pass of n samples lists its short items apart for k_gather_short (the
+// split form's FP32 maps).  That kernel splits the map block per wave, 16 ncomp values a
+// lane: with more than nine component tiles the workgroup form is the faster one for short
+// items too (1e5 uniform pointings at lmax 512, kmax 100: 2.25 against 2.46 ms; 2e5 at
+// lmax 256, kmax 64: 2.92 against 1.64 ms), unless the pass is too small to fill the chip
+// with workgroups (3000 scan samples at lmax 512, kmax 100: 113 against 53 us).  From 32 samples
+// per anchor on few items are short, and the launch is left out (lmax 64, kmax 4, 2e6 scan
+// samples, 55 per anchor: 201 us with it, 196 without; lmax 48, kmax 10, 4e5 uniform samples, 20
+// per anchor: 241 against 290).
+static inline bool sc_short_items(const sc_plan *p, int64_t n) {
+    if (p->prec == SC_FP64 || p->W != 8 || p->gather_mma != SC_MMA_SPLIT16 || p->gather_valu) return false;
+    if (n <= BIN_SMALL) return true;
+    const BinGeom g = sc_bin_geom(p);
+    return p->ncomp <= 144 && n < 32 * (int64_t)g.nkr * g.nkc;
+}
+// The same for the FP64 scatter: up to two component tiles (with more of them the wave form has
+// no more lanes to gain and the matrix form is as fast: kmax 20, lmax 256, 2e4 uniform samples
+// 1.20 against 1.31 ms, but kmax 127, lmax 128, 2e4 scan samples 485 against 341 us).
+static inline bool sc_short_items64(const sc_plan *p) { return p->prec == SC_FP64 && p->ncomp <= 32; }
 
 // Host-side helpers of sc_api.cpp: the calling thread's error message (sc_last_error),
 // and the argument checks and path choice of an interpolation.
