@@ -104,10 +104,11 @@ k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int rows, int cols,
     constexpr int NB = FftLen<S>::value > 0 ? FftLen<S>::value : PSI_NT * PSI_PT / G;  // LDS per transform
     static_assert(G == 1 || FftLen<S>::value > 0, "several transforms per wave need a compile-time plan");
     __shared__ double2 bufs[PPW][NB];
-    // compile-time plans: the twiddle bases of their passes; runtime plans: the whole table
+    // compile-time plans of FP32 cubes: the twiddle bases of their passes; FP64 cubes, which
+    // would show the rounding of the bases' powers, and runtime plans: the whole table
     using Run = FftRun<+1, NTS, PTS, S>;
-    constexpr bool PLAN = FftLen<S>::value > 0;
-    __shared__ double2 twl[PLAN ? Run::ntw : NB];
+    constexpr bool BASES = FftLen<S>::value > 0 && sizeof(T) == 4;
+    __shared__ double2 twl[BASES ? Run::ntw : NB];
     const int lane = threadIdx.x & (PSI_NT - 1), wv = threadIdx.x / PSI_NT;
     const int g = lane / NTS, tg = lane - g * NTS;
     const int pr = wv * G + g;  // pixel pair of the unit
@@ -116,7 +117,7 @@ k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int rows, int cols,
     const int ext = npsi + W - 1;
     const int nu = sc_map_ntile(cols) * (4 / PPW);  // units of a map row
     const int nunit = rows * nu;
-    if constexpr (PLAN) {
+    if constexpr (BASES) {
         if (pr == 0) Run::load_tw(twl, tw, tg);
     } else {
         for (int t = threadIdx.x; t < npsi; t += NWV * PSI_NT) twl[t] = tw[t];
@@ -142,7 +143,7 @@ k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int rows, int cols,
         const int row = u / nu, c0 = 2 * (PPW * (u - row * nu) + pr);
         const PV cur = nxt;
         if (u + (int)gridDim.x < nunit) fetch(nxt, u + gridDim.x);
-        if constexpr (!PLAN)
+        if constexpr (!BASES)
             for (int t = tg; t < npsi; t += NTS)
                 if (t > kmax && t < npsi - kmax) buf[t] = make_double2(0.0, 0.0);
 #pragma unroll
@@ -158,7 +159,7 @@ k_psi_cube(const T *__restrict__ maps, T *__restrict__ cube, int rows, int cols,
             }
         }
         __syncthreads();
-        if constexpr (PLAN)
+        if constexpr (BASES)
             Run::run_band(buf, twl, tg, kmax);  // the spectrum is zero for kmax < k < npsi - kmax
         else
             Run::run(buf, P, twl, tg, NTS);
@@ -337,7 +338,13 @@ template <typename T, typename S, int G>
 void launch_psi_cube(sc_plan *p) {
     constexpr int NWV = psi_waves<S>(G);
     const int64_t nunit = (int64_t)p->rows * sc_map_ntile(p->cols) * (4 / (NWV * G));
-    const unsigned nblk = (unsigned)(nunit < 16384 ? nunit : 16384);
+    // As many units for every workgroup, of up to 16384: with a part of them taking one more the
+    // rest of the chip waits (FP64 lmax 300, kmax 100: 817 us against 885 with 16384 whatever
+    // the count; lmax 128, kmax 100, 20 000 units: 243 us so).  Up to 1.5 a workgroup one each
+    // is better than two (166 us), at 1.9 it is not (135 against 121 us).
+    const int64_t most = 16384;
+    const int64_t each = 2 * nunit <= 3 * most ? 1 : (nunit + most - 1) / most;
+    const unsigned nblk = (unsigned)((nunit + each - 1) / each);
     hipLaunchKernelGGL((k_psi_cube<T, S, G>), dim3(nblk), dim3(PSI_NT * NWV), 0, p->stream, (const T *)p->maps,
                        (T *)p->cube, p->rows, p->cols, p->ncp, p->kmax, p->npsi, p->npst, p->W, p->ppsi, p->twpsi,
                        p->gpsi);
