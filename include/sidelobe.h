@@ -317,7 +317,10 @@ int sc_plan_stage_times(sc_plan *plan, double *ms, int64_t *launches, int nstage
 /*
  * Tunable parameters of a plan (chosen by the autotuner in the Python
  * package; defaults work everywhere).
- *   SC_PARAM_BIN_CHUNK          samples per gather/scatter work item, 16 .. 2^20 (default 256)
+ *   SC_PARAM_BIN_CHUNK          most samples per gather/scatter work item, 16 .. 2^20 (default 256).
+ *                               The kernels may take fewer: FP64 plans at most 64 in the gather
+ *                               and 128 in the adjoint scatter, passes of up to 4096 samples at
+ *                               most 256 (16 in the split gather); results do not depend on it
  *   SC_PARAM_GATHER_WGS_PER_CU  persistent gather/scatter workgroups per CU, 0 = as many as fit
  *   SC_PARAM_RING_RPT           northern rings per lane and recursion of the ring-sum kernel in use:
  *                               1 to 5 and 7 to 9 (SC_MIXED: 1 to 4); the plan starts with its

@@ -22,7 +22,8 @@ from . import _native as N
 
 RING_RPT = {N.SC_FP64: (1, 2, 3, 4, 5, 7, 8, 9), N.SC_F64MAPS_F32GATHER: (1, 2, 3, 4, 5, 7, 8, 9),
             N.SC_MIXED: (1, 2, 3, 4)}
-BIN_CHUNK = (128, 256, 512, 1024)
+# FP64 items hold at most 64 (gather) or 128 (scatter) samples: larger chunks are the same
+BIN_CHUNK = {N.SC_FP64: (256,), N.SC_F64MAPS_F32GATHER: (128, 256, 512, 1024), N.SC_MIXED: (128, 256, 512, 1024)}
 WGS_PER_CU = (0, 1)
 GATHER_WAVES = (4, 8)
 
@@ -94,7 +95,7 @@ def tune_plan(plan, alm, blm, ptg, reps: int = 3, use_cache: bool = True) -> dic
         times = {}
         # the workgroup shape is a choice of the FP32 product form only
         shapes = GATHER_WAVES if plan.get_param("gather_mma") == N.SC_MMA_FP32 else (4,)
-        for c in BIN_CHUNK:
+        for c in BIN_CHUNK[plan.precision]:
             for w in WGS_PER_CU:
                 for nw in shapes:
                     plan.set_param("bin_chunk", c)
