@@ -302,7 +302,8 @@ __global__ void k_bin_scatter(const double *__restrict__ ptg, int64_t n, BinGeom
 // A workgroup lists 256 PER anchors; the short ones among them get one reservation, so
 // neighbouring anchors stay neighbours and the counter sees one atomic per workgroup (8 ns each:
 // with one per wave of 64 anchors they took 0.35 ms of a pass of 1e5 uniform pointings at lmax
-// 512).  From 2^20 anchors on PER = 16; below 4, so that the workgroups still fill the chip.
+// 512).  PER = 16 from 2^20 anchors on, 4 from 2^18 on, else 1: few workgroups with many items
+// each take long (lmax 32, 2e6 scan samples: 12 us at 4, 5 at 1).
 constexpr int ITEMS_NT = 256;
 template <int ITEMS_PER>
 __global__ void __launch_bounds__(ITEMS_NT)
@@ -371,13 +372,13 @@ constexpr int SMALL_SPT = BIN_SMALL / SMALL_NT;
 constexpr int SMALL_HT = 2 * BIN_SMALL;  // slots: at most half of them used, so every probe ends
 constexpr int SMALL_HPT = SMALL_HT / SMALL_NT;
 
+// SPLIT: anchors of at most shortn samples go to the short list (the FP64 scatter); otherwise it
+// takes every item if shortn > 0 (the split gather).
+template <bool SPLIT>
 __global__ void __launch_bounds__(SMALL_NT)
 k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, const float *__restrict__ y,
             int4 *__restrict__ items, int chunk, int shortn, int64_t cap, int *__restrict__ totals) {
-    // the short list takes every item (the split gather, chunk = shortn), or the anchors of at
-    // most shortn samples
-    const bool all_short = shortn > 0 && chunk == shortn;
-    __shared__ int nshort;
+    __shared__ int nshort;  // SPLIT only
     __shared__ int hkey[SMALL_HT];
     __shared__ int hcnt[SMALL_HT];  // samples of the slot's key, then its first record
     __shared__ unsigned sh[SMALL_NT / 64];
@@ -387,7 +388,7 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
         hkey[tid + i * SMALL_NT] = KEYS_EMPTY;
         hcnt[tid + i * SMALL_NT] = 0;
     }
-    if (tid == 0) nshort = 0;
+    if (SPLIT && tid == 0) nshort = 0;
     double fu[SMALL_SPT], fv[SMALL_SPT], psi[SMALL_SPT];
     int key[SMALL_SPT], slot[SMALL_SPT], rank[SMALL_SPT];
 #pragma unroll
@@ -421,7 +422,7 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
 #pragma unroll
     for (int i = 0; i < SMALL_HPT; ++i) {
         const int c = hcnt[SMALL_HPT * tid + i];
-        const int listed = !all_short && c <= shortn ? 0 : (c + chunk - 1) / chunk;
+        const int listed = SPLIT && c <= shortn ? 0 : (c + chunk - 1) / chunk;
         v[i] = ((unsigned)listed << 16) | (unsigned)c;
         sum += v[i];
     }
@@ -441,23 +442,24 @@ k_bin_small(const double *__restrict__ ptg, int n, BinGeom g, BinSorted out, con
         if (c) {
             const int k = hkey[SMALL_HPT * tid + i];
             hcnt[SMALL_HPT * tid + i] = first;
-            if (!all_short && c <= shortn)
+            if (SPLIT && c <= shortn)
                 items[cap - 1 - atomicAdd(&nshort, 1)] = make_int4(k, first, c, 0);
             else
                 for (int q = 0; q * chunk < c; ++q)
-                    items[all_short ? cap - 1 - (it + q) : it + q] =
+                    items[!SPLIT && shortn > 0 ? cap - 1 - (it + q) : it + q] =
                         make_int4(k, first + q * chunk, c - q * chunk < chunk ? c - q * chunk : chunk, 0);
         }
         run += v[i];
     }
-    __syncthreads();
+    if (SPLIT) __syncthreads();  // nshort is complete
     if (tid == SMALL_NT - 1) {
         const int nit = (int)(run >> 16);
         totals[0] = n;
-        totals[1] = all_short ? 0 : nit;
+        totals[1] = !SPLIT && shortn > 0 ? 0 : nit;
         totals[2] = 0;
-        totals[3] = all_short ? nit : nshort;
+        totals[3] = SPLIT ? nshort : shortn > 0 ? nit : 0;
     }
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < SMALL_SPT; ++q) {
         if (key[q] < 0) continue;
@@ -525,9 +527,9 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     // (the deterministic scatter reads the per-anchor tables of the general path)
     w.small = n <= BIN_SMALL && !(use == SC_BIN_SCATTER && p->det_adjoint);
     if (w.small) {
-        hipLaunchKernelGGL(k_bin_small, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg, (int)n, g, w.sorted, y, w.items,
-                           use == SC_BIN_GATHER && shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap,
-                           w.totals);
+        const bool split = use == SC_BIN_SCATTER && shortn > 0;
+        hipLaunchKernelGGL(split ? k_bin_small<true> : k_bin_small<false>, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg, (int)n, g, w.sorted, y, w.items,
+                           !split && shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap, w.totals);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_fill_int, dim3(1024), dim3(256), 0, p->stream, w.count, nkeys, 0);
@@ -542,8 +544,9 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     hipLaunchKernelGGL(own ? k_scan_apply<true> : k_scan_apply<false>, dim3(nblk), dim3(SCAN_NT), 0, p->stream, w.count,
                        nkeys, w.sums, w.offs, chunk, shortn, w.totals);
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
-    const int64_t per = ITEMS_NT * (nkeys >= (1 << 20) ? 16 : 4);
-    hipLaunchKernelGGL(nkeys >= (1 << 20) ? k_bin_items<16> : k_bin_items<4>, dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count,
+    const int q = nkeys >= (1 << 20) ? 16 : nkeys >= (1 << 18) ? 4 : 1;
+    const int64_t per = ITEMS_NT * q;
+    hipLaunchKernelGGL(q == 16 ? k_bin_items<16> : q == 4 ? k_bin_items<4> : k_bin_items<1>, dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count,
                        w.offs, nkeys, w.items, chunk, shortn, w.cap, w.totals);
     return hipGetLastError();
 }

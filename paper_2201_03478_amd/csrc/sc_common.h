@@ -311,15 +311,15 @@ static inline BinGeom sc_bin_geom(const sc_plan *p) {
 // lane: with more than nine component tiles the workgroup form is the faster one for short
 // items too (1e5 uniform pointings at lmax 512, kmax 100: 2.25 against 2.46 ms; 2e5 at
 // lmax 256, kmax 64: 2.92 against 1.64 ms), unless the pass is too small to fill the chip
-// with workgroups (3000 scan samples at lmax 512, kmax 100: 113 against 53 us).  From 32 samples
-// per anchor on few items are short, and the launch is left out (lmax 64, kmax 4, 2e6 scan
-// samples, 55 per anchor: 201 us with it, 196 without; lmax 48, kmax 10, 4e5 uniform samples, 20
-// per anchor: 241 against 290).
+// with workgroups (3000 scan samples at lmax 512, kmax 100: 113 against 53 us).  From 16 samples
+// per anchor on the launch is left out: a scan then has few short items, for which it takes 5 us
+// (lmax 64, kmax 4: 1e6 scan samples 137 us with it, 129 without; 2e6: 201 and 193; evenly
+// spread samples gain from it up to some 25 per anchor: lmax 48, kmax 10, 4e5, 241 against 290).
 static inline bool sc_short_items(const sc_plan *p, int64_t n) {
     if (p->prec == SC_FP64 || p->W != 8 || p->gather_mma != SC_MMA_SPLIT16 || p->gather_valu) return false;
     if (n <= BIN_SMALL) return true;
     const BinGeom g = sc_bin_geom(p);
-    return p->ncomp <= 144 && n < 32 * (int64_t)g.nkr * g.nkc;
+    return p->ncomp <= 144 && n < 16 * (int64_t)g.nkr * g.nkc;
 }
 // The same for the FP64 scatter: up to two component tiles (with more of them the wave form has
 // no more lanes to gain and the matrix form is as fast: kmax 20, lmax 256, 2e4 uniform samples

@@ -1,6 +1,6 @@
 """The scan of the binning: one or two kernels after the per-block sums (up to 1024 blocks of 4096
 anchors each block adds up its predecessors itself), lists of work items by 1024 or 4096 anchors
-a workgroup, and passes with and without a list of short items (32 samples per anchor).
+a workgroup, and passes with and without a list of short items (16 samples per anchor).
 
 Every sample must stand exactly once in the anchor order, and the time-ordered data must equal
 that of a batch, whose gather takes all items in one list, bit for bit.
@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 # anchors: 32 -> 9 000, 300 -> 0.8e6, 360 -> 1.2e6 (4096 a workgroup), 660 -> 3.6e6 and 720 ->
 # 4.25e6 (three kernels)
-@pytest.mark.parametrize("L,n", [(32, 4097), (32, 250_000), (32, 400_000), (300, 50_000), (360, 50_000), (660, 30_000),
+@pytest.mark.parametrize("L,n", [(32, 4097), (32, 100_000), (32, 157_000), (32, 158_000), (32, 400_000), (300, 50_000), (360, 50_000), (660, 30_000),
                                  (720, 30_000)])
 def test_every_sample_once(L, n):
     K = 2
