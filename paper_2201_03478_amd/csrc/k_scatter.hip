@@ -551,16 +551,23 @@ k_scatter_mfma64(const int4 *__restrict__ items, const int *__restrict__ totals,
     }
 }
 
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
 // Anchors of at most BIN_SHORT_SC64 samples, one wave each: the sum over the samples in
-// registers, one atomic per (tap, component), 64 of them at a time (CW components of 64 / CW
-// taps).  The matrix form costs such an item its barriers and LDS fills, about as much as the
+// registers, one atomic per (tap, component), 64 of them at a time: CW components of 64 / CW
+// neighbouring columns of one row, which share sectors (a column of 64 / CW rows instead: 1.6
+// times the time at kmax 0), and whose theta weight is the same for the whole wave (read from a
+// lane).  The matrix form costs such an item its barriers and LDS fills, about as much as the
 // atomics of four samples: 1e5 uniform pointings, W = 14, lmax 512, kmax 0: 1.70 ms with it,
-// 0.50 here, 0.92 sample by sample; kmax 8: 3.2, 2.4 and 2.6.
+// 0.47 here, 0.92 sample by sample; kmax 8: 3.2, 2.3 and 2.6.
 template <int W, int NS, int CW>
 __device__ __forceinline__ void scatter64_samples(const BinRec *__restrict__ rc, int ns, const double *__restrict__ y,
                                                   double *__restrict__ gm, int cols, int ncp, int ncomp, double beta,
                                                   int lane) {
-    constexpr int TP = 64 / CW;  // taps at a time
+    constexpr int CP = 64 / CW, NG = (W + CP - 1) / CP;  // columns at a time, groups of them
     double w[NS], ys[NS];
     double2 e1[NS];
 #pragma unroll
@@ -586,13 +593,26 @@ __device__ __forceinline__ void scatter64_samples(const BinRec *__restrict__ rc,
             val[s] = ys[s] * ((c & 1) ? z.y : z.x);
         }
         const bool on = c < ncomp && c != 1;  // basis_1 = sin 0 = 0
-#pragma unroll 2
-        for (int t0 = 0; t0 < W * W; t0 += TP) {
-            const int t = t0 + lane / CW, i = t / W, j = t - i * W;
-            double a = 0.0;
+        double vj[NG][NS];
 #pragma unroll
-            for (int s = 0; s < NS; ++s) a = fma(__shfl(w[s], i) * __shfl(w[s], W + j), val[s], a);
-            if (on && t < W * W) atomic_add(gm + ((size_t)i * cols + j) * ncp + c, a);
+        for (int g = 0; g < NG; ++g) {
+            const int j = g * CP + lane / CW;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) vj[g][s] = __shfl(w[s], W + (j < W ? j : 0)) * val[s];
+        }
+        for (int i = 0; i < W; ++i) {
+            double wi[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) wi[s] = read_lane(w[s], i);
+            double *row = gm + (size_t)i * cols * ncp + c;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const int j = g * CP + lane / CW;
+                double a = 0.0;
+#pragma unroll
+                for (int s = 0; s < NS; ++s) a = fma(wi[s], vj[g][s], a);
+                if (on && j < W) atomic_add(row + (size_t)j * ncp, a);
+            }
         }
     }
 }
@@ -853,16 +873,19 @@ bool sc_scatter64_supported(const sc_plan *p) {
 // Whether binning a pass of n samples pays.  Sample by sample the scatter is bound by its
 // atomics, one request per tap and 64-byte sector of a pixel's components at 45 ps (W = 14, 2e4
 // to 4e5 samples: 8.8 ns a sample up to kmax 3, 17 up to 7, 26 at 8, 53 at 20; W = 8: 3.3).  The
-// binning costs a launch of 12 us up to BIN_SMALL samples, from there its seven kernels and
+// binning costs a launch of 12 us up to BIN_SMALL samples, from there six or seven kernels and
 // 10.5 ps per anchor (34 us at lmax 64, 56 at 512, 132 at 1024), and only samples that share
-// anchors give it back: spread evenly, the same atomics remain.  So it runs where it is at most
-// half of the per-sample form's time.  Near the line, lmax 64, kmax 4, 5000 samples: uniform
-// 113 us sample by sample and 118 binned, scan 145 and 74.
+// anchors give it back: spread evenly, the same atomics remain, save that the columns of a row of
+// one- or two-component pixels share sectors (k_scatter_short64).  So it runs where it is at most
+// half of the per-sample form's time, or 1 / 1.2 of it with such pixels.  Near the line (samples
+// evenly spread | a scan; sample by sample, binned, us): lmax 64, kmax 4, 5000: 113, 118 | 145, 74;
+// kmax 0, 2500: 41, 38 | 69, 41; 5000: 73, 67 | 125, 60; lmax 512, 10,000, kmax 0: 120, 128 | 182,
+// 114, kmax 2: 130, 185 | 165, 138; lmax 1024, 20,000, kmax 0: 251, 313 | 319, 230.
 bool sc_scatter64_pays(const sc_plan *p, int64_t n) {
     const BinGeom g = sc_bin_geom(p);
     const double direct = 45e-6 * (double)n * p->W * p->W * ((p->ncomp + 7) / 8);
     const double bin = n <= BIN_SMALL ? 12.0 : 34.0 + 10.5e-6 * (double)g.nkr * (double)g.nkc;
-    return direct > 2.0 * bin;
+    return direct > (p->ncomp <= 2 ? 1.2 : 2.0) * bin;
 }
 hipError_t sc_launch_scatter64(sc_plan *p, const double *y, double *gmaps) {
     switch (p->W) {

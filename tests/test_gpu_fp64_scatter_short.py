@@ -47,7 +47,7 @@ def _gradients(plan, a, b, p, y):
     (14, 0, 3001), (14, 7, 4096), (14, 15, 4096), (16, 1, 4095), (12, 8, 4000), (10, 16, 4096), (8, 15, 4096),
     (6, 23, 4096), (14, 23, 4096), (16, 39, 2000),
     (4, 0, 100_000), (4, 15, 30_000), (6, 1, 50_000), (8, 7, 20_000), (10, 3, 20_000), (12, 6, 6000), (14, 0, 9000),
-    (14, 1, 30_001), (14, 7, 8191), (14, 15, 4097), (14, 16, 5000), (16, 15, 4500), (16, 23, 4097)])
+    (14, 0, 2000), (14, 1, 30_001), (14, 7, 8191), (14, 15, 4097), (14, 16, 5000), (16, 15, 4500), (16, 23, 4097)])
 def test_binned_scatter_matches_the_per_sample_path(monkeypatch, width, kmax, n):
     L = 48
     a = torch.from_numpy(W.sky_alm(L, 41)).cuda()
@@ -65,7 +65,7 @@ def test_binned_scatter_matches_the_per_sample_path(monkeypatch, width, kmax, n)
         assert np.max(np.abs(g - r)) <= 1e-12 * np.max(np.abs(r))
 
 
-@pytest.mark.parametrize("width,kmax,n", [(14, 0, 2000), (14, 0, 5000), (4, 0, 20_000), (8, 3, 4096)])
+@pytest.mark.parametrize("width,kmax,n", [(14, 0, 1500), (14, 0, 4097), (14, 1, 5000), (4, 0, 20_000), (8, 3, 4096)])
 def test_small_passes_are_not_binned(width, kmax, n):
     L = 48
     a = torch.from_numpy(W.sky_alm(L, 41)).cuda()
