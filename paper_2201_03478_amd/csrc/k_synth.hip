@@ -195,27 +195,36 @@ k_ring_sums(const double2 *__restrict__ alm, const double2 *__restrict__ blm, FT
         // to the same registers, so neither the loads nor the recursion need register moves.
         // The last chunk is rounded up to whole iterations: steps past lmax have zero
         // weights and coefficients.
-        // Rescaling is checked once per 32 steps, outside their loop (a check in every iteration
-        // costs launches of few waves 5%: lmax 256, kmax 0: 22.7 against 21.6 us): one step
+        // Rescaling is checked once per 32 steps, up to 8 rings per lane outside their loop (a
+        // check in every iteration costs launches of few waves 5%: lmax 256, kmax 0: 22.7 against
+        // 21.6 us; with 9 the second loop takes 256 registers instead of 240, so that two waves
+        // leave no room on a SIMD for the binning's first kernels, which a convolution runs
+        // beside this one: lmax 512, kmax 100, 1e7 samples: 5.25 against 5.16 ms): one step
         // grows |u| by at most ~2^11, so 32 steps stay inside the 2^424 left below overflow,
         // and what a ring accumulates between passing 2^600 and its rescale (true values below
         // 2^{-600 + 352}) is dropped harmlessly with the scaled sums.
         RecCoef a0 = rec_load(0, cA, cBt, cWp, cWm), a1 = rec_load(1, cA, cBt, cWp, cWm);
-        for (int t0 = 0; t0 < nl; t0 += 32) {
-            const int t1 = t0 + 32 < nl ? t0 + 32 : nl;
-            for (int t = t0; t < t1; t += 4) {
-                const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
-                __builtin_amdgcn_sched_barrier(0);
-                rec_step<RPT>(a0, x, u, up, fp, fm);
-                rec_step<RPT>(a1, x, u, up, fp, fm);
-                const int tn = (t + 4) & 63;  // last iteration: harmless re-read
-                a0 = rec_load(tn, cA, cBt, cWp, cWm);
-                a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
-                __builtin_amdgcn_sched_barrier(0);
-                rec_step<RPT>(b0, x, u, up, fp, fm);
-                rec_step<RPT>(b1, x, u, up, fp, fm);
+        auto four = [&](int t) {
+            const RecCoef b0 = rec_load(t + 2, cA, cBt, cWp, cWm), b1 = rec_load(t + 3, cA, cBt, cWp, cWm);
+            __builtin_amdgcn_sched_barrier(0);
+            rec_step<RPT>(a0, x, u, up, fp, fm);
+            rec_step<RPT>(a1, x, u, up, fp, fm);
+            const int tn = (t + 4) & 63;  // last iteration: harmless re-read
+            a0 = rec_load(tn, cA, cBt, cWp, cWm);
+            a1 = rec_load(tn + 1, cA, cBt, cWp, cWm);
+            __builtin_amdgcn_sched_barrier(0);
+            rec_step<RPT>(b0, x, u, up, fp, fm);
+            rec_step<RPT>(b1, x, u, up, fp, fm);
+        };
+        constexpr int IN = RPT > 8 ? 4 : 32;
+        for (int t0 = 0; t0 < nl; t0 += IN) {
+            if (IN == 4) {
+                four(t0);
+            } else {
+                const int t1 = t0 + IN < nl ? t0 + IN : nl;
+                for (int t = t0; t < t1; t += 4) four(t);
             }
-            if (fast) continue;
+            if (fast || (IN < 32 && (t0 & 28) != 28 && t0 + IN < nl)) continue;
             bool low = false;
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
