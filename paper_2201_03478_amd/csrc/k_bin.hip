@@ -528,7 +528,8 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     w.small = n <= BIN_SMALL && !(use == SC_BIN_SCATTER && p->det_adjoint);
     if (w.small) {
         const bool split = use == SC_BIN_SCATTER && shortn > 0;
-        hipLaunchKernelGGL(split ? k_bin_small<true> : k_bin_small<false>, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg, (int)n, g, w.sorted, y, w.items,
+        hipLaunchKernelGGL(split ? k_bin_small<true> : k_bin_small<false>, dim3(1), dim3(SMALL_NT), 0, p->stream, ptg,
+                           (int)n, g, w.sorted, y, w.items,
                            !split && shortn > 0 ? shortn : std::min(chunk, BIN_CHUNK), shortn, w.cap, w.totals);
         return hipGetLastError();
     }
@@ -546,7 +547,8 @@ hipError_t sc_launch_binning(sc_plan *p, const double *ptg, int64_t n, const flo
     hipLaunchKernelGGL(k_bin_scatter, dim3(gs), dim3(bs), 0, p->stream, ptg, n, g, w.key, w.rank, w.offs, w.sorted, y);
     const int q = nkeys >= (1 << 20) ? 16 : nkeys >= (1 << 18) ? 4 : 1;
     const int64_t per = ITEMS_NT * q;
-    hipLaunchKernelGGL(q == 16 ? k_bin_items<16> : q == 4 ? k_bin_items<4> : k_bin_items<1>, dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count,
-                       w.offs, nkeys, w.items, chunk, shortn, w.cap, w.totals);
+    hipLaunchKernelGGL(q == 16 ? k_bin_items<16> : q == 4 ? k_bin_items<4> : k_bin_items<1>,
+                       dim3((unsigned)((nkeys + per - 1) / per)), dim3(ITEMS_NT), 0, p->stream, w.count, w.offs, nkeys,
+                       w.items, chunk, shortn, w.cap, w.totals);
     return hipGetLastError();
 }

@@ -1238,9 +1238,9 @@ hipError_t launch_mfma_any(sc_plan *p, void *tod) {
 }
 }  // namespace
 
-// FP32 maps: W = 8.  FP64 maps: every even width (k_gather64.hip stages the block
-// in component chunks); the VALU form above is kept for W = 8 as a comparison
-// (env SC_GATHER_PATH=valu).
+// FP32 maps: W = 8.  FP64 maps: every even width (k_gather64.hip, one wave per item with
+// its operands from L2); the VALU form above is kept for W = 8 as a comparison (env
+// SC_GATHER_PATH=valu).
 bool sc_gather_binned_supported(const sc_plan *p) {
     if (p->prec == SC_FP64) return sc_gather_mfma64_supported(p->W) && p->ncomp <= 256;
     return p->W == 8 && p->ncomp <= 256;
